@@ -442,16 +442,10 @@ lev_status gemm_ab(int64_t M, int64_t N, int64_t K, double alpha, const double* 
                    "dgemm");
 }
 
-// Pivoted Cholesky of B (d x d, overwritten) into st, then perm / R / rank.
+// Pivoted Cholesky of B (d x d, overwritten): perm, R and rank.
 lev_status pivchol_into(double* B, int64_t d, double zeta, const lev::PivCholState& st, int64_t* rank,
-                        int32_t* perm, double* R, double* partial, hipStream_t s, int fixed = 0,
-                        const double* ref_r00 = nullptr) {
-  // the panel path (d > 256) tracks progress in flags; the single-workgroup
-  // path does not read them
-  if (d > 256) LEV_HIP(lev::launch_fill_zero(st.flags, 64 * sizeof(int32_t), s));
-  LEV_HIP(lev::launch_pivchol(B, d, zeta, st, rank, partial, s, fixed, ref_r00));
-  LEV_HIP(lev::launch_pivchol_finalize(d, st, rank, perm, R, s));
-  return LEV_OK;
+                        int32_t* perm, double* R, hipStream_t s, int fixed = 0, const double* ref_r00 = nullptr) {
+  return hip_check(lev::launch_pivchol(B, d, zeta, st, rank, perm, R, s, fixed, ref_r00), "pivchol");
 }
 
 // Q (m x d) = an orthonormal basis of the first r columns of X (the other
@@ -466,7 +460,7 @@ lev_status cholqr2(int64_t m, int64_t d, const double* X, const double* Rc, cons
   LEV_HIP(lev::launch_trsm_z(d, d, Rc, r, b.I, b.Rinv, err, s));  // Rc11^{-1}, zero past r
   LEV_TRY(gemm_ab(m, d, d, 1.0, X, d, 1, b.Rinv, d, 1, 0.0, b.Qa, b.partial, s));
   LEV_TRY(gemm_ab(d, d, m, 1.0, b.Qa, 1, d, b.Qa, d, 1, 0.0, b.Bq, b.partial, s));
-  LEV_TRY(pivchol_into(b.Bq, d, 0.0, b.stf, b.rf, b.permf, b.Rf, b.partial, s, /*fixed=*/1));
+  LEV_TRY(pivchol_into(b.Bq, d, 0.0, b.stf, b.rf, b.permf, b.Rf, s, /*fixed=*/1));
   LEV_HIP(lev::launch_identity(d, b.I, s));
   LEV_HIP(lev::launch_trsm_z(d, d, b.Rf, b.rf, b.I, b.Rinv, err, s));
   LEV_TRY(gemm_ab(m, d, d, 1.0, b.Qa, d, 1, b.Rinv, d, 1, 0.0, Q, b.partial, s));
@@ -484,14 +478,14 @@ lev_status enqueue_rank(const double* At, int64_t m, int64_t d, double zeta, con
                         int32_t* perm, double* R, int64_t* rank, hipStream_t s, RefineBufs* rf = nullptr) {
   // Gram B = A~^T A~ (d x d): the tiles on and above the diagonal, mirrored
   LEV_HIP(lev::launch_gram_dense(LEV_F64, At, m, d, d, lev::gram_sketch_splits(m, d), b.partial, b.B, s));
-  if (zeta >= kZetaGram || rf == nullptr) return pivchol_into(b.B, d, zeta, b.pc, rank, perm, R, b.partial, s);
+  if (zeta >= kZetaGram || rf == nullptr) return pivchol_into(b.B, d, zeta, b.pc, rank, perm, R, s);
 
   RefineBufs& f = *rf;
   int32_t* err = b.pc.err;
   f.stf.err = err;
   f.st2.err = err;
   // stage 1: the columns the Gram resolves
-  LEV_TRY(pivchol_into(b.B, d, kZetaGram, b.pc, f.r1, f.perm1, f.R1, b.partial, s));
+  LEV_TRY(pivchol_into(b.B, d, kZetaGram, b.pc, f.r1, f.perm1, f.R1, s));
   LEV_HIP(lev::launch_gather_split(m, d, f.perm1, f.r1, At, f.X1, f.X2, s));
   LEV_TRY(cholqr2(m, d, f.X1, f.R1, f.r1, f, f.Q, err, s));
   // the rest projected off range(Q1) twice; R's rows 0..r1-1 = Q1^T X
@@ -503,7 +497,7 @@ lev_status enqueue_rank(const double* At, int64_t m, int64_t d, double zeta, con
   LEV_HIP(lev::launch_add2(d * d, f.Rtop, f.W1, f.W2, s));
   // stage 2: pivoting on the residual's Gram, cutoff zeta * R_00 of stage 1
   LEV_TRY(gemm_ab(d, d, m, 1.0, f.X2, 1, d, f.X2, d, 1, 0.0, f.Bq, f.partial, s));
-  LEV_TRY(pivchol_into(f.Bq, d, zeta, f.st2, f.r2, f.perm2, f.R2, b.partial, s, 0, b.pc.r00));
+  LEV_TRY(pivchol_into(f.Bq, d, zeta, f.st2, f.r2, f.perm2, f.R2, s, 0, b.pc.r00));
   LEV_HIP(lev::launch_gather_split(m, d, f.perm2, f.r2, f.X2, f.X1, nullptr, s));  // X1 <- the stage-2 columns
   LEV_TRY(cholqr2(m, d, f.X1, f.R2, f.r2, f, f.Q, err, s));
   LEV_TRY(gemm_ab(d, d, m, 1.0, f.Q, 1, d, f.X2, d, 1, 0.0, f.Rbot, f.partial, s));
@@ -844,9 +838,7 @@ lev_status estimate_exact(const lev_matrix* A, const lev_params* p, int variant,
     LEV_HIP(lev::launch_fill_zero(eb.C64, sizeof(double) * (size_t)(d * d), s));
   }
   LEV_HIP(lev::launch_gather_bk(d, sv.perm, rank, eb.C64, eb.rb2.B, s));
-  if (d > 256) LEV_HIP(lev::launch_fill_zero(eb.rb2.pc.flags, 64 * sizeof(int32_t), s));
-  LEV_HIP(lev::launch_pivchol(eb.rb2.B, d, 0.0, eb.rb2.pc, eb.rank2, eb.rb2.partial, s));
-  LEV_HIP(lev::launch_pivchol_finalize(d, eb.rb2.pc, eb.rank2, eb.perm2, eb.R2, s));
+  LEV_TRY(pivchol_into(eb.rb2.B, d, 0.0, eb.rb2.pc, eb.rank2, eb.perm2, eb.R2, s));
   LEV_HIP(lev::launch_compose_perm(d, sv.perm, eb.perm2, eb.permc, s));
   LEV_HIP(lev::launch_identity(d, eb.I, s));
   LEV_HIP(lev::launch_form_z(variant, d, d, eb.R2, eb.rank2, eb.permc, eb.I, sv.Z64, Zpack, err, s));

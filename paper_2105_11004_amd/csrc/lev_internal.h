@@ -117,13 +117,12 @@ constexpr int32_t kErrSolveWait = 2;
 // fixed != 0: no pivoting (step J takes column J), i.e. the plain Cholesky
 // of B, stopping at the first non-positive diagonal.  ref_r00 (device, may
 // be null): the R_00 the cutoff zeta * R_00 refers to, instead of the first
-// pivot's own.
+// pivot's own.  Writes the rank, perm (int32[d], unpivoted columns ascending
+// after the rank) and R_out (d x d, pivoted order, zero below the diagonal
+// and below the rank).
 hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState& st, int64_t* rank_out,
-                          double* gemm_partial, hipStream_t s, int fixed = 0, const double* ref_r00 = nullptr);
-// Writes perm (int32[d], unpivoted columns ascending after the rank) and
-// R_out (d x d, pivoted order, zero below the diagonal and below the rank).
-hipError_t launch_pivchol_finalize(int64_t d, const PivCholState& st, const int64_t* rank,
-                                   int32_t* perm_out, double* R_out, hipStream_t s);
+                          int32_t* perm_out, double* R_out, hipStream_t s, int fixed = 0,
+                          const double* ref_r00 = nullptr);
 
 // Z = R11^{-1} G_k[0:r, 0:k] in FP64 (R pivoted d x d, ld = d), r read from
 // the device.  Z64 is d x k (rows >= r zeroed).  For d > 256 the solve runs

@@ -17,9 +17,10 @@
 // Rank rule (the cutoff test of Section 7): pivoting stops at the first J
 // with R_JJ <= zeta * R_00 (or a non-positive Schur diagonal); r = J.
 //
-// Two implementations: d <= 256 runs entirely in one workgroup with the
-// Schur complement in registers (below); larger d uses panels of NB pivots
-// (one workgroup) and rank-NB Schur updates on the matrix cores.
+// Three implementations: d <= 64 runs in one wave with the Gram and R in LDS
+// and writes the pivoted R itself (one launch); d <= 256 runs entirely in one
+// workgroup with the Schur complement in registers; larger d uses panels of NB
+// pivots (one workgroup) and rank-NB Schur updates on the matrix cores.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -55,6 +56,43 @@ __device__ __forceinline__ double wave_max_f64(double v) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
   return __hiloint2double(hi, lo);
+}
+
+// Max over the 64 lanes of a signed word, in every lane of the result
+// (uniform).
+__device__ __forceinline__ int wave_max_i32(int v) {
+  int m;
+  asm volatile(
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_readlane_b32 %1, %0, 63"
+      : "+v"(v), "=s"(m));
+  return m;
+}
+
+// The largest v over the 64 lanes (no NaN) and the lowest lane holding it.
+// The high words are ordered like the values while the largest is positive,
+// and a word maximum is one instruction a step where a double takes three;
+// lanes that share the largest high word are told apart by a second pass.
+// (Where no value is positive, any of them may be returned: every caller
+// then only looks at its sign.)
+__device__ __forceinline__ double wave_argmax(double v, int* lane_out) {
+  const int key = __double2hiint(v);
+  const int top = wave_max_i32(key);
+  uint64_t hit = __ballot(key == top);
+  if ((hit & (hit - 1)) != 0) {
+    const double x = key == top ? v : -INFINITY;
+    const double m = wave_max_f64(x);
+    hit = __ballot(x == m);
+  }
+  const int l = __builtin_ctzll(hit);
+  *lane_out = l;
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also
@@ -539,6 +577,141 @@ __global__ __launch_bounds__(768) void pivchol_small_kernel(const double* __rest
   }
 }
 
+// 1 / sqrt(x) (hardware estimate and two Newton steps) and sqrt(x) from it
+// with one correction step; x positive, finite and normal.
+__device__ __forceinline__ void rsqrt_sqrt(double x, double* inv, double* root) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * fma(-0.5 * x * y, y, 1.5);
+  y = y * fma(-0.5 * x * y, y, 1.5);
+  const double r = x * y;
+  *root = fma(fma(-r, r, x), 0.5 * y, r);
+  *inv = y;
+}
+
+// ---------------------------------------------------------------------------
+// d <= 64: the whole factorisation by one wave, lane c owning column c, with
+// the Gram and R in LDS (no barrier in the pivot loop, no global memory read
+// in it).  Step J needs only row p of the Gram and the rows of R so far: R's
+// entries of a lane's column sit in registers for the finished blocks of 16
+// rows and are read from LDS for the block under way, so the step is one
+// short loop body per block.  The other waves load the Gram and write the
+// pivoted R.  Bound: the chain of one pivot step in one wave (maximum, LDS
+// read, FMAs, reciprocal root; about 0.45 us).  At d = 64, 48 pivots: 26 us in
+// one launch, against 44 + 5 us for the workgroup form below and the
+// permutation's own launch; past 64 columns a lane would hold two.
+constexpr int kWaveD = 64;
+constexpr int kWaveS = kWaveD + 2;  // row stride of the Gram in LDS
+constexpr int kWaveR = kWaveD + 1;  // column stride of R in LDS
+
+// a0 -= sum over even t of b[T0 + t] r[t], a1 over odd t, t < 8.
+template <int T0>
+__device__ __forceinline__ void fma_bcast8(double& a0, double& a1, double b, const double* r) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%2, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %4 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%2, %5 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%2, %7 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %8 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%2, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %10 row_newbcast:%18 row_mask:0xf bank_mask:0xf"
+      : "+v"(a0), "+v"(a1)
+      : "v"(b), "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(r[3]), "v"(r[4]), "v"(r[5]), "v"(r[6]), "v"(r[7]), "n"(T0),
+        "n"(T0 + 1), "n"(T0 + 2), "n"(T0 + 3), "n"(T0 + 4), "n"(T0 + 5), "n"(T0 + 6), "n"(T0 + 7));
+}
+
+__global__ __launch_bounds__(256) void pivchol_wave_kernel(const double* __restrict__ B, int d, double zeta,
+                                                           int fixed, const double* __restrict__ ref_r00,
+                                                           PivCholState st, int64_t* __restrict__ rank_out,
+                                                           int32_t* __restrict__ perm_out,
+                                                           double* __restrict__ R_out) {
+  __shared__ double Sc[kWaveD * kWaveS];
+  __shared__ double Rc[kWaveD * kWaveR];
+  __shared__ int perm_s[kWaveD];
+  __shared__ int rank_s;
+  const int tid = threadIdx.x, lane = tid & 63;
+#pragma unroll 4
+  for (int e = tid; e < d * d; e += 256) {
+    const int i = e / d;
+    Sc[i * kWaveS + (e - i * d)] = B[e];
+  }
+  for (int e = tid; e < kWaveD * kWaveR; e += 256) Rc[e] = 0.0;
+  __syncthreads();
+  if (tid < 64) {
+    const bool in = lane < d;
+    double dg = in ? Sc[lane * kWaveS + lane] : -INFINITY;
+    double r00 = ref_r00 != nullptr ? *ref_r00 : 0.0;
+    double zr2 = (zeta * r00) * (zeta * r00);
+    double rp[kWaveD - 16];  // the lane's column of R, finished blocks
+    int J = 0;
+    bool run = true, chosen = false;
+#pragma unroll
+    for (int blk = 0; blk < kWaveD / 16; ++blk) {
+#pragma unroll 1
+      for (int jj = 0; jj < 16 && run; ++jj) {
+        if (J >= d) {
+          run = false;
+          break;
+        }
+        // the largest diagonal, ties to the lowest column (a NaN never wins)
+        const double cv = (fixed == 0 || lane == J) && dg == dg ? dg : -INFINITY;
+        int p;
+        const double pv = wave_argmax(cv, &p);
+        double inv, rjj;
+        rsqrt_sqrt(pv, &inv, &rjj);
+        if (J == 0 && ref_r00 == nullptr) {
+          r00 = pv > 0.0 ? rjj : 0.0;
+          zr2 = (zeta * r00) * (zeta * r00);
+        }
+        if (!(pv > 0.0) || !(pv > zr2)) {
+          run = false;
+          break;
+        }
+        double a0 = in ? Sc[p * kWaveS + lane] : 0.0, a1 = 0.0;
+        double own[16];
+        const double bcur = Rc[p * kWaveR + 16 * blk + (lane & 15)];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) own[t] = Rc[lane * kWaveR + 16 * blk + t];
+#pragma unroll
+        for (int q = 0; q < blk; ++q) {
+          const double bq = Rc[p * kWaveR + 16 * q + (lane & 15)];
+          fma_bcast8<0>(a0, a1, bq, rp + 16 * q);
+          fma_bcast8<8>(a0, a1, bq, rp + 16 * q + 8);
+        }
+        fma_bcast8<0>(a0, a1, bcur, own);
+        fma_bcast8<8>(a0, a1, bcur, own + 8);
+        double v = (a0 + a1) * inv;
+        const double nd = fma(-v, v, dg);
+        const bool live = dg != -INFINITY, piv = lane == p;
+        v = piv ? rjj : (live ? v : 0.0);
+        dg = piv ? -INFINITY : (live ? nd : dg);
+        chosen = chosen || piv;
+        Rc[lane * kWaveR + J] = v;
+        if (lane == 0) perm_s[J] = p;
+        ++J;
+      }
+      if (blk + 1 < kWaveD / 16) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) rp[16 * blk + t] = Rc[lane * kWaveR + 16 * blk + t];
+      }
+    }
+    const unsigned long long rest = __ballot(in && !chosen);
+    if (in && !chosen) perm_s[J + __popcll(rest & ((1ull << lane) - 1ull))] = lane;
+    if (lane == 0) {
+      rank_s = J;
+      *st.r00 = r00;
+      *rank_out = J;
+    }
+  }
+  __syncthreads();
+  const int r = rank_s;
+  if (tid < d) perm_out[tid] = perm_s[tid];
+  for (int e = tid; e < d * d; e += 256) {
+    const int j = e / d, t = e - j * d;
+    R_out[e] = (j < r && t >= j) ? Rc[perm_s[t] * kWaveR + j] : 0.0;
+  }
+}
+
 // perm: pivots, then the unselected columns ascending.  R_out: pivoted,
 // upper triangular, rows >= r zero.  One launch: every workgroup rebuilds
 // the permutation in LDS (a ballot count of the unselected columns per wave,
@@ -649,15 +822,28 @@ __global__ __launch_bounds__(256) void schur_update_kernel(double* __restrict__ 
 
 }  // namespace
 
+static hipError_t launch_pivchol_finalize(int64_t d, const PivCholState& st, const int64_t* rank,
+                                   int32_t* perm_out, double* R_out, hipStream_t s) {
+  pivchol_finalize_kernel<<<(unsigned)((d + kFinalRows - 1) / kFinalRows), kMaxD, 0, s>>>(d, st, rank, perm_out,
+                                                                                          R_out);
+  return hipGetLastError();
+}
+
 hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState& st, int64_t* rank_out,
-                          double* gemm_partial, hipStream_t s, int fixed, const double* ref_r00) {
-  (void)gemm_partial;
+                          int32_t* perm_out, double* R_out, hipStream_t s, int fixed, const double* ref_r00) {
   if (d <= 0 || d > kMaxD) return hipErrorInvalidValue;
+  if (d <= kWaveD) {
+    pivchol_wave_kernel<<<1, 256, 0, s>>>(B, (int)d, zeta, fixed, ref_r00, st, rank_out, perm_out, R_out);
+    return hipGetLastError();
+  }
   if (d <= kSmallD) {
     const int waves = small_rects((int)d) + 1;
     pivchol_small_kernel<<<1, 64 * waves, 0, s>>>(B, (int)d, zeta, st, rank_out, fixed, ref_r00);
-    return hipGetLastError();
+    return launch_pivchol_finalize(d, st, rank_out, perm_out, R_out, s);
   }
+  // the panels track their progress in flags
+  hipError_t e = launch_fill_zero(st.flags, 64 * sizeof(int32_t), s);
+  if (e != hipSuccess) return e;
   const int threads = (int)(((d + 64 * kPanelCols - 1) / (64 * kPanelCols)) * 64);
   for (int64_t J0 = 0; J0 < d; J0 += NB) {
     if (fixed)
@@ -669,19 +855,11 @@ hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState&
       const double* Rp = st.Rrows + J0 * d;
       const unsigned tiles = (unsigned)((d + kSchurTile - 1) / kSchurTile);
       schur_update_kernel<<<dim3(tiles, tiles), 256, 0, s>>>(B, d, Rp, st.flags);
-      hipError_t e = hipGetLastError();
+      e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_pivchol_finalize(int64_t d, const PivCholState& st, const int64_t* rank,
-                                   int32_t* perm_out, double* R_out, hipStream_t s) {
-  if (d <= 0 || d > kMaxD) return hipErrorInvalidValue;
-  pivchol_finalize_kernel<<<(unsigned)((d + kFinalRows - 1) / kFinalRows), kMaxD, 0, s>>>(d, st, rank, perm_out,
-                                                                                          R_out);
-  return hipGetLastError();
+  return launch_pivchol_finalize(d, st, rank_out, perm_out, R_out, s);
 }
 
 }  // namespace lev
