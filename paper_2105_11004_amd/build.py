@@ -25,7 +25,7 @@ LIB = PKG / "liblev.so"
 ARCH = "gfx950"
 
 SOURCES = ["sketch.hip", "gauss.hip", "gemm.hip", "pivchol.hip", "rrqr.hip", "trsm.hip", "rownorm.hip",
-           "rownorm_bf16.hip", "rownorm_csr.hip", "bwd.hip", "xgemm.hip", "gram_csr.hip", "srht.hip", "qless.hip", "precond.hip",
+           "rownorm_bf16.hip", "rownorm_csr.hip", "bwd.hip", "xgemm.hip", "gram_tall.hip", "gram_csr.hip", "srht.hip", "qless.hip", "precond.hip",
            "probe.hip", "lev_api.cpp"]
 
 COMMON_FLAGS = [
