@@ -21,9 +21,9 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <type_traits>
 
 #include "lev_internal.h"
+#include "tall_stage.h"
 
 namespace lev {
 namespace {
@@ -52,62 +52,6 @@ __device__ __forceinline__ bool unit_of(int u, int d, int* i_out, int* J_out) {
   return false;
 }
 
-// What LDS holds of an element: BF16 is widened to FP32 when staged, the rest
-// to FP64 when read.
-template <typename TI>
-using lds_t = std::conditional_t<std::is_same_v<TI, double>, double, float>;
-
-template <typename TI, int TB>
-struct StepRegs {  // a thread's part of a step: 16-byte pieces of A
-  static constexpr int kElts = 16 / (int)sizeof(TI);
-  static constexpr int kPieces = (kRows * 64 * TB / kElts + kThreads - 1) / kThreads;
-  uint4 v[kPieces];
-};
-
-template <typename TI, int TB>
-__device__ __forceinline__ void load_step(StepRegs<TI, TB>& r, const TI* __restrict__ A, int64_t k0, int64_t ke, int d,
-                                          int64_t ld) {
-  using R = StepRegs<TI, TB>;
-  constexpr int per = 64 * TB / R::kElts;  // pieces per row
-#pragma unroll
-  for (int q = 0; q < R::kPieces; ++q) {
-    const int e = threadIdx.x + kThreads * q;
-    const int c = (e % per) * R::kElts;
-    const int64_t row = k0 + e / per;
-    // rows are 16-byte multiples, so a piece that starts below d ends below
-    // ld; what it holds past d reaches only outputs past d, which are not
-    // stored
-    const bool in = e / per < kRows && row < ke && c < d;
-    const uint4 x = *reinterpret_cast<const uint4*>(A + (in ? row * ld + c : 0));
-    r.v[q] = in ? x : uint4{0, 0, 0, 0};
-  }
-}
-
-template <typename TI, int TB>
-__device__ __forceinline__ void store_step(const StepRegs<TI, TB>& r, lds_t<TI>* __restrict__ L) {
-  using R = StepRegs<TI, TB>;
-  constexpr int per = 64 * TB / R::kElts, stride = 64 * TB + 16;
-#pragma unroll
-  for (int q = 0; q < R::kPieces; ++q) {
-    const int e = threadIdx.x + kThreads * q;
-    if (R::kPieces * kThreads > kRows * per && e >= kRows * per) continue;
-    lds_t<TI>* dst = L + (e / per) * stride + (e % per) * R::kElts;
-    if constexpr (std::is_same_v<TI, __hip_bfloat16>) {
-      const uint32_t w[4] = {r.v[q].x, r.v[q].y, r.v[q].z, r.v[q].w};
-      float f[8];
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        f[2 * h] = __uint_as_float(w[h] << 16);
-        f[2 * h + 1] = __uint_as_float(w[h] & 0xffff0000u);
-      }
-      reinterpret_cast<float4*>(dst)[0] = make_float4(f[0], f[1], f[2], f[3]);
-      reinterpret_cast<float4*>(dst)[1] = make_float4(f[4], f[5], f[6], f[7]);
-    } else {
-      *reinterpret_cast<uint4*>(dst) = r.v[q];
-    }
-  }
-}
-
 // Index of (i, j), i <= j, in the packed upper triangle of d columns.
 __device__ __forceinline__ int64_t packed(int i, int j, int d) { return (int64_t)i * d - (int64_t)i * (i - 1) / 2 + (j - i); }
 
@@ -116,9 +60,9 @@ __device__ __forceinline__ int64_t packed(int i, int j, int d) { return (int64_t
 template <typename TI, int TB, int U, int KG>
 __global__ __launch_bounds__(kThreads) void gram_tall_kernel(const TI* __restrict__ A, int64_t n, int d, int64_t ld,
                                                              int64_t chunk, double* __restrict__ partial) {
-  constexpr int stride = 64 * TB + 16;
+  constexpr int stride = tall_stride(TB);
   constexpr int UG = kWaves / KG;  // waves that share a row group
-  __shared__ __align__(16) lds_t<TI> L[2][kRows * stride];
+  __shared__ __align__(16) tall_lds_t<TI> L[2][kRows * stride];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ug = wave % UG, kg = wave / UG;
@@ -135,21 +79,22 @@ __global__ __launch_bounds__(kThreads) void gram_tall_kernel(const TI* __restric
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[u][b] = v4d{0.0, 0.0, 0.0, 0.0};
 
-  StepRegs<TI, TB> regs;
+  TallStep<TI, TB, kRows, kThreads> regs;
   if (kb < ke) {
-    load_step<TI, TB>(regs, A, kb, ke, d, ld);
-    store_step<TI, TB>(regs, L[0]);
+    tall_load(regs, A, kb, ke, d, ld);
+    tall_store(regs, ke - kb, L[0]);
   }
   __syncthreads();
   int buf = 0;
   for (int64_t k0 = kb; k0 < ke; k0 += kRows) {
     const bool more = k0 + kRows < ke;
-    if (more) load_step<TI, TB>(regs, A, k0 + kRows, ke, d, ld);
+    if (more) tall_load(regs, A, k0 + kRows, ke, d, ld);
+    __builtin_amdgcn_sched_barrier(0);  // (the loads stay ahead of the products)
     // operand of lane l for rows k .. k + 3: row k + l / 16
-    const lds_t<TI>* base = L[buf] + (4 * kg + g) * stride + c;
+    const tall_lds_t<TI>* base = L[buf] + (4 * kg + g) * stride + c;
     double oa[2], ob[2][4];
     auto read = [&](int u, int s, int slot) __attribute__((always_inline)) {
-      const lds_t<TI>* row = base + s * (4 * KG * stride);
+      const tall_lds_t<TI>* row = base + s * (4 * KG * stride);
       oa[slot] = (double)row[16 * ui[u]];
 #pragma unroll
       for (int b = 0; b < 4; ++b) ob[slot][b] = (double)row[64 * uj[u] + 16 * b];
@@ -173,7 +118,7 @@ __global__ __launch_bounds__(kThreads) void gram_tall_kernel(const TI* __restric
       }
     }
     // the other buffer was last read before the previous barrier
-    if (more) store_step<TI, TB>(regs, L[buf ^ 1]);
+    if (more) tall_store(regs, ke - k0 - kRows, L[buf ^ 1]);
     __syncthreads();
     buf ^= 1;
   }

@@ -10,7 +10,12 @@
 // or after kmax steps.  The scores are then ||e_i^T A P_k R_k^{-1}||^2 by
 // the same Z and pass 2 as the other modes.
 //
-// Per step: one pass kernel over A writes per-workgroup partial sums of b
+// Dense A with d <= 256 columns: the rows b are formed for a block of 16
+// columns a pass, those of largest remaining norm (qless_block_pass_kernel);
+// the steps then go on as long as the next pivot's row is there.  Every result
+// is the same quantity; only the number of passes falls.
+//
+// Else, per step: one pass kernel over A writes per-workgroup partial sums of b
 // (dense: 16-byte row vectors with the pivot element as weight; CSR: the
 // rows that hold column p, found in a first sweep over the column ids), and
 // one single-workgroup step kernel sums them in a fixed order, forms row j
@@ -25,6 +30,7 @@
 #include <algorithm>
 
 #include "lev_internal.h"
+#include "tall_stage.h"
 
 namespace lev {
 namespace {
@@ -362,8 +368,246 @@ __global__ __launch_bounds__(kStepThreads) void qless_step_kernel(int64_t d, int
   }
 }
 
+// ---- dense A, d <= 256: blocks of columns --------------------------------------
+//
+// A pass over A costs its bytes whatever it computes for 16 columns: the
+// products A^T [a_P], |P| = 16, are one MFMA column block (n d 16 FP64
+// multiply-adds, 0.13 ms at 2^20 x 256 against 0.18 ms for the read).  The next
+// pivots are mostly among the columns of largest remaining norm, so a block
+// serves several steps: at 2^20 x 256 FP32, rank 16, three block passes of
+// 225 us in place of 16 passes of 244 us (4.98 -> 1.5 ms a call).  Two
+// workgroups a CU with 32 rows of A in flight each (one with 64 rows: 265 us).
+constexpr int kBlk = 16;
+constexpr int kBlkD = 256;
+constexpr int kBlkWaves = 8;
+constexpr int kBlkThreads = 64 * kBlkWaves;
+constexpr int kBlkGroups = 512;  // two workgroups a CU
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// ctl: [0] steps done, [2] stop flag, [3] arrivals of the sum kernel
+struct BlockState {
+  double* s;       // d: remaining norms^2
+  double* rows;    // d x d: row p = A^T a_p where have[p]
+  int32_t* have;   // d
+  int32_t* sel;    // d
+  int32_t* block;  // kBlk: the columns of the next pass
+  int32_t* piv;
+  double* Rrow;
+  double* sums;    // kBlk x d: the last pass
+  int64_t* ctl;
+  double* dctl;
+};
+
+// partial[g][j][c] = sum over the rows of workgroup g of A[i][P_j] A[i][c].
+// Rows are staged as in the Gram of a tall A; a wave owns the 16-column blocks
+// w and w + 8 of the result.
+template <typename T, int TB>
+__global__ __launch_bounds__(kBlkThreads) void qless_block_pass_kernel(const T* __restrict__ A, int64_t n, int d,
+                                                                       int64_t ld, int64_t chunk, BlockState st,
+                                                                       double* __restrict__ partial) {
+  constexpr int stride = tall_stride(TB);
+  constexpr int ROWS = std::is_same_v<T, double> ? 16 : 32;  // two workgroups a CU
+  constexpr int NB = (4 * TB + kBlkWaves - 1) / kBlkWaves;
+  __shared__ __align__(16) tall_lds_t<T> L[2][ROWS * stride];
+  if (st.ctl[2] != 0) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int pc = st.block[c];
+  const int64_t kb = (int64_t)blockIdx.x * chunk, ke = std::min<int64_t>(n, kb + chunk);
+  v4d acc[NB];
+  int blk[NB];  // (past the last block the last one again, not stored)
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
+    blk[b] = wave + kBlkWaves * b < 4 * TB ? wave + kBlkWaves * b : 4 * TB - 1;
+  }
+  TallStep<T, TB, ROWS, kBlkThreads> regs;
+  if (kb < ke) {
+    tall_load(regs, A, kb, ke, d, ld);
+    tall_store(regs, ke - kb, L[0]);
+  }
+  __syncthreads();
+  int buf = 0;
+  for (int64_t k0 = kb; k0 < ke; k0 += ROWS) {
+    const bool more = k0 + ROWS < ke;
+    if (more) tall_load(regs, A, k0 + ROWS, ke, d, ld);
+    __builtin_amdgcn_sched_barrier(0);  // (the loads stay ahead of the products)
+    const tall_lds_t<T>* base = L[buf] + g * stride;
+#pragma unroll
+    for (int k4 = 0; k4 < ROWS; k4 += 4) {
+      const tall_lds_t<T>* row = base + k4 * stride;
+      const double pb = (double)row[pc];
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)row[16 * blk[b] + c], pb, acc[b], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) tall_store(regs, ke - k0 - ROWS, L[buf ^ 1]);
+    __syncthreads();
+    buf ^= 1;
+  }
+  double* out = partial + (int64_t)blockIdx.x * kBlk * d;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int col = 16 * (wave + kBlkWaves * b) + g + 4 * v;
+      if (wave + kBlkWaves * b < 4 * TB && col < d) out[c * d + col] = acc[b][v];
+    }
+}
+
+// Sums the partials of a pass (outputs values, 64 a workgroup, in four
+// interleaved groups added in a fixed order); the workgroup that comes last
+// then takes the steps whose rows are known and chooses the next block.
+// squares: the partials are the columns' norms^2 (the first pass).
+__global__ __launch_bounds__(256) void qless_block_step_kernel(int d, int64_t kmax, int groups, int outputs,
+                                                               const double* __restrict__ partial, double zeta,
+                                                               int squares, BlockState st) {
+  __shared__ double part[4][64];
+  __shared__ int last;
+  __shared__ double ls[kBlkD];
+  __shared__ double vbuf[4];
+  __shared__ int ibuf[4];
+  if (!squares && st.ctl[2] != 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  {
+    const int o = blockIdx.x * 64 + lane;
+    double a = 0.0;
+    if (o < outputs) {
+#pragma unroll 8
+      for (int z = wave; z < groups; z += 4) a += partial[(int64_t)z * outputs + o];
+    }
+    part[wave][lane] = a;
+    __syncthreads();
+    if (wave == 0 && o < outputs) st.sums[o] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+  }
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) last = atomicAdd(reinterpret_cast<unsigned long long*>(&st.ctl[3]), 1ull) == gridDim.x - 1 ? 1 : 0;
+  __syncthreads();
+  if (last == 0) return;
+  __threadfence();
+
+  const int c = tid;  // this thread's column
+  const bool in = c < d;
+  int64_t j = squares ? 0 : st.ctl[0];
+  double s = -1.0, r00 = 0.0;
+  bool sel = true, have = false;
+  if (in && squares) {
+    s = __hip_atomic_load(&st.sums[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sel = false;
+  } else if (in) {
+    s = st.s[c];
+    sel = st.sel[c] != 0;
+    have = st.have[c] != 0;
+    r00 = st.dctl[0];
+  }
+  if (!squares) {
+    // the pass's rows take their places
+    r00 = st.dctl[0];
+    for (int q = 0; q < kBlk; ++q) {
+      const int p = st.block[q];
+      if (in) st.rows[p * d + c] = __hip_atomic_load(&st.sums[q * d + c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      have = have || c == p;
+    }
+  }
+  bool stop = false;
+  for (;;) {
+    if (j >= kmax) {
+      stop = true;
+      break;
+    }
+    // the largest remaining norm, ties to the lowest column (a NaN never wins)
+    double v = in && !sel && s > -1.0 ? s : -1.0;
+    int vi = v > -1.0 ? c : kBlkD;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double w = __shfl_xor(v, o);
+      const int wi = __shfl_xor(vi, o);
+      if (w > v || (w == v && wi < vi)) {
+        v = w;
+        vi = wi;
+      }
+    }
+    __syncthreads();
+    if (lane == 0) {
+      vbuf[wave] = v;
+      ibuf[wave] = vi;
+    }
+    __syncthreads();
+    double best = vbuf[0];
+    int p = ibuf[0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w)
+      if (vbuf[w] > best || (vbuf[w] == best && ibuf[w] < p)) {
+        best = vbuf[w];
+        p = ibuf[w];
+      }
+    const double rjj = p < kBlkD ? sqrt(fmax(best, 0.0)) : 0.0;
+    if (j == 0) r00 = rjj;
+    if (p >= kBlkD || !(rjj > 0.0) || rjj <= zeta * r00) {
+      stop = true;
+      break;
+    }
+    // is the pivot's row known?
+    __syncthreads();
+    if (c == p) ibuf[0] = have ? 1 : 0;
+    __syncthreads();
+    if (ibuf[0] == 0) break;
+    double r = 0.0;
+    if (in && c == p) {
+      r = rjj;
+    } else if (in && !sel) {
+      double b = st.rows[p * d + c];
+      for (int64_t i = 0; i < j; ++i) b -= st.Rrow[i * d + p] * st.Rrow[i * d + c];
+      r = b / rjj;
+      s -= r * r;
+    }
+    if (in) st.Rrow[j * d + c] = r;
+    if (c == p) {
+      sel = true;
+      st.piv[j] = p;
+    }
+    ++j;
+    __threadfence_block();
+    __syncthreads();  // the row is read back by every thread
+  }
+  // the next block: the kBlk unselected columns without a row of largest
+  // remaining norm (the pivot first); fewer are padded with the first
+  const double key = in && !sel && !have && s > -1.0 ? s : -1.0;
+  ls[tid] = key;
+  __syncthreads();
+  if (!stop) {
+    int rank = 0, live = 0;
+    for (int o = 0; o < kBlkD; ++o) {
+      const double w = ls[o];
+      live += w > -1.0 ? 1 : 0;
+      rank += (w > key || (w == key && o < c)) ? 1 : 0;
+    }
+    if (key > -1.0 && rank < kBlk) st.block[rank] = c;
+    if (key > -1.0 && rank == 0)
+      for (int q = live; q < kBlk; ++q) st.block[q] = c;
+  }
+  if (in) {
+    st.s[c] = s;
+    st.sel[c] = sel ? 1 : 0;
+    st.have[c] = have ? 1 : 0;
+  }
+  if (tid == 0) {
+    st.ctl[0] = j;
+    st.ctl[2] = stop ? 1 : 0;
+    st.ctl[3] = 0;
+    st.dctl[0] = r00;
+  }
+}
+
 // perm = the pivots, then the other columns ascending; R (d x d, pivoted
-// order) from the rows; rank.
+// order) from the rows; rank.  Every workgroup rebuilds the permutation (a
+// ballot count of the unselected columns), the first writes it, and each
+// writes kFinalRows rows of R.
+constexpr int kFinalRows = 8;
+
 __global__ __launch_bounds__(kStepThreads) void qless_finalize_kernel(int64_t d, const int64_t* __restrict__ ctl,
                                                                       const int32_t* __restrict__ sel,
                                                                       const int32_t* __restrict__ piv,
@@ -371,21 +615,26 @@ __global__ __launch_bounds__(kStepThreads) void qless_finalize_kernel(int64_t d,
                                                                       int32_t* __restrict__ perm,
                                                                       double* __restrict__ R,
                                                                       int64_t* __restrict__ rank) {
-  __shared__ int32_t pm[1024];
+  __shared__ int32_t pm[kStepThreads];
+  __shared__ int cnt[kStepThreads / 64];
+  const int c = threadIdx.x, lane = c & 63, w = c >> 6;  // d <= kStepThreads
   const int64_t k = ctl[0];
-  if (threadIdx.x == 0) {
-    int64_t q = 0;
-    for (; q < k; ++q) pm[q] = piv[q];
-    for (int64_t c = 0; c < d; ++c)
-      if (!(c < d && sel[c])) pm[q++] = (int32_t)c;
-    *rank = k;
-  }
+  const bool left = c < d && sel[c] == 0;
+  const unsigned long long bal = __ballot(left);
+  if (lane == 0) cnt[w] = __popcll(bal);
   __syncthreads();
-  for (int64_t c = threadIdx.x; c < d; c += kStepThreads) perm[c] = pm[c];
-  for (int64_t e = threadIdx.x; e < d * d; e += kStepThreads) {
-    const int64_t i = e / d, jp = e % d;
-    R[e] = (i < k && jp >= i) ? Rrow[i * d + pm[jp]] : 0.0;
+  int64_t at = k + __popcll(bal & ((1ull << lane) - 1ull));
+  for (int q = 0; q < w; ++q) at += cnt[q];
+  if (c < k) pm[c] = piv[c];
+  if (left) pm[at] = c;
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    if (c < d) perm[c] = pm[c];
+    if (c == 0) *rank = k;
   }
+  const int64_t i0 = (int64_t)blockIdx.x * kFinalRows;
+  for (int64_t i = i0; i < i0 + kFinalRows && i < d; ++i)
+    if (c < d) R[i * d + c] = (i < k && c >= i) ? Rrow[i * d + pm[c]] : 0.0;
 }
 
 template <typename T>
@@ -399,6 +648,19 @@ hipError_t pass_dense(const void* A, int64_t n, int64_t d, int64_t ld, const int
     qless_pass_dense_kernel<T, 2><<<groups, kPassThreads, 0, st>>>(a, n, d, ld, ctl, squares, rows, partial);
   else
     qless_pass_dense_kernel<T, 1><<<groups, kPassThreads, 0, st>>>(a, n, d, ld, ctl, squares, rows, partial);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t block_pass(const void* A, int64_t n, int64_t d, int64_t ld, int groups, const BlockState& bs,
+                      double* partial, hipStream_t st) {
+  const T* a = static_cast<const T*>(A);
+  const int64_t chunk = ((n + groups - 1) / groups + 3) / 4 * 4;
+  auto kern = d <= 64    ? qless_block_pass_kernel<T, 1>
+              : d <= 128 ? qless_block_pass_kernel<T, 2>
+              : d <= 192 ? qless_block_pass_kernel<T, 3>
+                         : qless_block_pass_kernel<T, 4>;
+  kern<<<groups, kBlkThreads, 0, st>>>(a, n, (int)d, ld, chunk, bs, partial);
   return hipGetLastError();
 }
 
@@ -424,6 +686,12 @@ int qless_groups(int64_t n, bool csr) {
 }
 
 size_t qless_ws_doubles(int64_t n, int64_t d, int64_t kmax, bool csr) {
+  if (!csr && d <= kBlkD)
+    // s, Rrow, partial (of the squares or of a block), rows, sums, dctl (2)
+    // and, as doubles, sel, have, piv, block and ctl
+    return (size_t)d + (size_t)kmax * d +
+           (size_t)std::max(qless_groups(n, false), kBlkGroups * kBlk) * d + (size_t)d * d + (size_t)kBlk * d + 2 +
+           2 * (size_t)d + (size_t)kmax + kBlk + 4;
   // s, Rrow, partial, dctl (2) and, as doubles, sel, piv and ctl
   return (size_t)d + (size_t)kmax * d + (size_t)qless_groups(n, csr) * d + 2 + (size_t)d + (size_t)kmax + 4;
 }
@@ -440,10 +708,14 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
   int32_t* sel = reinterpret_cast<int32_t*>(dctl + 2);
   int32_t* piv = sel + d;
   int64_t* ctl = reinterpret_cast<int64_t*>(reinterpret_cast<double*>(sel) + d + kmax);
+  if (!csr && d <= kBlkD)  // behind the block form's dctl (below)
+    ctl = reinterpret_cast<int64_t*>(partial + (size_t)std::max(groups, kBlkGroups * kBlk) * d + d * d + kBlk * d + 2);
   hipError_t e = launch_fill_zero(ctl, 4 * sizeof(int64_t), st);
   if (e != hipSuccess) return e;
-  e = launch_fill_zero(partial, sizeof(double) * (size_t)groups * d, st);
-  if (e != hipSuccess) return e;
+  if (n == 0) {  // no pass writes them
+    e = launch_fill_zero(partial, sizeof(double) * (size_t)groups * d, st);
+    if (e != hipSuccess) return e;
+  }
   auto pass = [&](int squares) -> hipError_t {
     if (n == 0) return hipSuccess;
     if (csr) {
@@ -464,12 +736,41 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
     }
   };
   if ((e = pass(1)) != hipSuccess) return e;
+  if (!csr && d <= kBlkD) {
+    BlockState bs;
+    bs.s = s;
+    bs.Rrow = Rrow;
+    bs.rows = partial + (size_t)std::max(groups, kBlkGroups * kBlk) * d;
+    bs.sums = bs.rows + d * d;
+    bs.dctl = bs.sums + kBlk * d;
+    bs.ctl = ctl;
+    bs.sel = reinterpret_cast<int32_t*>(ctl + 4);
+    bs.have = bs.sel + d;
+    bs.piv = bs.have + d;
+    bs.block = bs.piv + kmax;
+    qless_block_step_kernel<<<(unsigned)((d + 63) / 64), 256, 0, st>>>((int)d, kmax, groups, (int)d, partial, zeta, 1, bs);
+    const int bg = (int)std::max<int64_t>(1, std::min<int64_t>(kBlkGroups, (n + 63) / 64));
+    // every pass takes at least one step, so kmax of them always suffice; those
+    // after the stop return at once
+    for (int64_t j = 0; j < kmax; ++j) {
+      if (n > 0) {
+        e = in.dtype == 0   ? block_pass<double>(in.values, n, d, in.ld, bg, bs, partial, st)
+            : in.dtype == 1 ? block_pass<float>(in.values, n, d, in.ld, bg, bs, partial, st)
+                            : block_pass<__hip_bfloat16>(in.values, n, d, in.ld, bg, bs, partial, st);
+        if (e != hipSuccess) return e;
+      }
+      qless_block_step_kernel<<<(unsigned)(kBlk * d + 63) / 64, 256, 0, st>>>((int)d, kmax, bg, (int)(kBlk * d), partial,
+                                                                            zeta, 0, bs);
+    }
+    qless_finalize_kernel<<<(unsigned)((d + kFinalRows - 1) / kFinalRows), kStepThreads, 0, st>>>(d, ctl, bs.sel, bs.piv, Rrow, perm_out, R_out, rank_out);
+    return hipGetLastError();
+  }
   qless_step_kernel<<<1, kStepThreads, 0, st>>>(d, kmax, groups, partial, zeta, s, sel, Rrow, ctl, dctl, piv, 1);
   for (int64_t j = 0; j < kmax; ++j) {
     if ((e = pass(0)) != hipSuccess) return e;
     qless_step_kernel<<<1, kStepThreads, 0, st>>>(d, kmax, groups, partial, zeta, s, sel, Rrow, ctl, dctl, piv, 0);
   }
-  qless_finalize_kernel<<<1, kStepThreads, 0, st>>>(d, ctl, sel, piv, Rrow, perm_out, R_out, rank_out);
+  qless_finalize_kernel<<<(unsigned)((d + kFinalRows - 1) / kFinalRows), kStepThreads, 0, st>>>(d, ctl, sel, piv, Rrow, perm_out, R_out, rank_out);
   return hipGetLastError();
 }
 
