@@ -25,6 +25,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lev_internal.h"
 
 namespace lev {
@@ -113,27 +115,118 @@ __device__ __forceinline__ double max8_f64(double v) {
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 7);
   return __hiloint2double(hi, lo);
 }
+__device__ __forceinline__ int max8_i32(int v) {
+  int m;
+  asm volatile(
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_readlane_b32 %1, %0, 7"
+      : "+v"(v), "=s"(m));
+  return m;
+}
+
+// 1 / sqrt(x) (hardware estimate and two Newton steps) and sqrt(x) from it
+// with one correction step; x positive, finite and normal.
+__device__ __forceinline__ void rsqrt_sqrt(double x, double* inv, double* root) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * fma(-0.5 * x * y, y, 1.5);
+  y = y * fma(-0.5 * x * y, y, 1.5);
+  const double r = x * y;
+  *root = fma(fma(-r, r, x), 0.5 * y, r);
+  *inv = y;
+}
+
+// acc -= b[T] r0, acc1 -= b[T] r1 for T = T0 .. T0 + N - 1, b[T] taken from
+// lane T of each 16-lane row by the FMA itself (the s_nop covers a vector
+// write of b just before).
+template <int T0>
+__device__ __forceinline__ void fma_bcast1(double& a0, double& a1, double b, double r0, double r1) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      : "+v"(a0), "+v"(a1)
+      : "v"(b), "v"(r0), "v"(r1), "n"(T0));
+}
+template <int T0>
+__device__ __forceinline__ void fma_bcast4(double& a0, double& a1, double b, const double* r0, const double* r1) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%2, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %4 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%2, %5 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %6 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%2, %7 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %8 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%2, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+      : "+v"(a0), "+v"(a1)
+      : "v"(b), "v"(r0[0]), "v"(r1[0]), "v"(r0[1]), "v"(r1[1]), "v"(r0[2]), "v"(r1[2]), "v"(r0[3]), "v"(r1[3]),
+        "n"(T0), "n"(T0 + 1), "n"(T0 + 2), "n"(T0 + 3));
+}
+
+// a0 -= sum_{t < J} b_t r0[t], a1 likewise, t ascending; b_t of t < 16 in
+// lane t of each row of blo, of t >= 16 in lane t - 16 of bhi.
+template <int J, int T = 0>
+__device__ __forceinline__ void fma_rows(double& a0, double& a1, double blo, double bhi, const double* r0,
+                                         const double* r1) {
+  if constexpr (T + 4 <= J) {
+    fma_bcast4<T % 16>(a0, a1, T < 16 ? blo : bhi, r0 + T, r1 + T);
+    fma_rows<J, T + 4>(a0, a1, blo, bhi, r0, r1);
+  } else if constexpr (T < J) {
+    fma_bcast1<T % 16>(a0, a1, T < 16 ? blo : bhi, r0[T], r1[T]);
+    fma_rows<J, T + 1>(a0, a1, blo, bhi, r0, r1);
+  }
+}
+
+// f(integral_constant J) for J = 0 .. N - 1 until one returns false: the
+// panel's steps with J a constant, so that the entries of R stay in registers.
+template <int N, int J = 0, typename F>
+__device__ __forceinline__ bool static_all(F&& f) {
+  if constexpr (J < N) {
+    if (!f(std::integral_constant<int, J>{})) return false;
+    return static_all<N, J + 1>(f);
+  }
+  return true;
+}
 
 // One panel of NB pivot steps.  Thread t owns the adjacent columns 2t and
 // 2t + 1 (at most 8 waves for d <= 1024): every pivot step runs two
-// reductions and two barriers whose cost is paid per wave, so half as many
+// reductions and a barrier whose cost is paid per wave, so half as many
 // waves, each with twice the column work, halve that part of the step.  The
 // lane's candidate is the larger of its two diagonals (ties to the lower
 // column), the wave's the lowest lane holding the wave max, the workgroup's
 // the lowest wave holding the overall max: ties go to the lowest column.
 // flags[0] = done, flags[1] = pivots computed so far.
+//
+// The pivot column's entries of the panel so far are read as two values a lane
+// and broadcast by the FMAs themselves (fma_rows), not as LDS broadcasts per
+// entry.  Every column's last SH entries are kept in LDS, so that each wave
+// reads the pivot's as soon as it knows the pivot, with no second barrier; with
+// SH = 16 (d > kShareD, where 32 do not fit) the column's owner posts those of
+// the first half behind a second barrier in the second half's steps.  The
+// latency of the pivot's row of S (about 800 cycles) is covered by the sums,
+// which are added to it last.  Bound: the chain of one step, about 2000 cycles
+// (wave maximum 440, barrier 90, the waves' maximum 365, the row of S 800, the
+// entry and diagonal 300).  A panel of 32: 26.5 us at d = 512, 30.7 at 520, 40.0
+// at 1024 (33.2, 38.3 and 44.7 with LDS broadcasts, two barriers a step, a
+// scaled square root and division, and maxima over doubles).
 constexpr int kPanelCols = 2;
 constexpr int kPanelThreads = kMaxD / kPanelCols;
 constexpr int kPanelWaves = kPanelThreads / 64;
+constexpr int kShareD = 600;
+// stride of a column's entries in LDS (the writes spread over the banks)
+constexpr int rc_stride(int sh) { return sh + 1; }
 
 // FIXED: the pivot order is the identity (step J's only candidate is column J).
-template <bool FIXED>
+template <bool FIXED, int SH>
 __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const double* __restrict__ S, int64_t d,
                                                                       double zeta, int64_t J0,
                                                                       PivCholState st,
                                                                       int64_t* __restrict__ rank_out,
                                                                       const double* __restrict__ ref_r00) {
-  __shared__ double bc[NB];
+  static_assert(SH == 16 || SH == NB, "a half or the whole panel");
+  extern __shared__ double rc[];  // d x rc_stride(SH)
+  __shared__ double post[16];     // SH = 16: the pivot's entries of the first half
   __shared__ double wv[2][kPanelWaves];
   __shared__ int wi[2][kPanelWaves];
 
@@ -142,14 +235,14 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
   const int nwaves = blockDim.x >> 6;
   const int c0 = kPanelCols * tid;  // columns c0, c0 + 1
   if (J0 > 0 && st.flags[0] != 0) return;
+  const int di = (int)d, Ji = (int)J0;  // d <= kMaxD: 32-bit offsets below
 
-  double dg[2];
-  bool alive[2];
+  double dg[2];  // -inf: not alive (a pivot before, past d, or NaN)
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int c = c0 + q;
-    dg[q] = (c < d) ? ((J0 == 0) ? S[(int64_t)c * d + c] : st.diag[c]) : -INFINITY;
-    alive[q] = (c < d) && (dg[q] != -INFINITY);
+    dg[q] = (c < di) ? ((J0 == 0) ? S[(int64_t)c * d + c] : st.diag[c]) : -INFINITY;
+    dg[q] = fmax(dg[q], -INFINITY);
   }
   double r00 = ref_r00 != nullptr ? *ref_r00 : ((J0 == 0) ? 0.0 : *st.r00);
   // the cutoff sqrt(pv) > zeta r00 is tested as pv > (zeta r00)^2, so that
@@ -158,35 +251,34 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
   double zr2 = (zeta * r00) * (zeta * r00);
 
   double rp0[NB], rp1[NB];
-#pragma unroll
-  for (int t = 0; t < NB; ++t) rp0[t] = rp1[t] = 0.0;
-
-  int64_t J = J0;
-  bool stop = false;
-  bool active = true;  // uniform across the workgroup
-  const int di = (int)d;  // d <= kMaxD: 32-bit offsets below
-  double* rrow = st.Rrows + J0 * d + c0;  // row J of R at this thread's columns
-  // Constant trip count (no break) so the loop unrolls fully and rp0[],
-  // rp1[] stay in registers.
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    if (active && J >= d) active = false;
-    if (!active) continue;
+  int J = Ji;
+  int mine = 0;  // wave 0: lane j keeps pivot j
+  const int q0 = c0 < di ? c0 : 0, q1 = c0 + 1 < di ? c0 + 1 : 0;  // in bounds
+  const bool pair = c0 + 1 < di && (di & 1) == 0;                  // 16-byte aligned (d even, c0 even)
+  const bool whole = static_all<NB>([&](auto jc) __attribute__((always_inline)) -> bool {
+    constexpr int j = decltype(jc)::value;
+    if (J >= di) return false;
     // the lane's candidate (a column no longer alive holds -inf; fixed
     // order: the only candidate of step J is column J); a NaN diagonal
     // never wins
     const double m0 = (!FIXED || c0 == J) ? dg[0] : -INFINITY;
     const double m1 = (!FIXED || c0 + 1 == J) ? dg[1] : -INFINITY;
-    const bool second = (m1 > m0) || (m0 != m0);
+    const bool second = m1 > m0;
     const double mv = second ? m1 : m0;
-    const int mc = c0 + (second ? 1 : 0);
-    const double wmax = wave_max_f64(mv);
-    const uint64_t hit = __ballot(mv == wmax);
-    const int hl = hit != 0 ? (__ffsll((unsigned long long)hit) - 1) : 0;
-    const int hc = __builtin_amdgcn_readlane(mc, hl);
-    if (lane == 0) {
-      wv[j & 1][wave] = hit != 0 ? wmax : -INFINITY;
-      wi[j & 1][wave] = hit != 0 ? hc : 0x7fffffff;
+    // the wave's: high words first (as in wave_argmax); the winning lane posts
+    {
+      const int key = __double2hiint(mv);
+      const int top = wave_max_i32(key);
+      uint64_t hit = __ballot(key == top);
+      if ((hit & (hit - 1)) != 0) {
+        const double x = key == top ? mv : -INFINITY;
+        const double m = wave_max_f64(x);
+        hit = __ballot(x == m);
+      }
+      if (lane == __builtin_ctzll(hit)) {
+        wv[j & 1][wave] = mv;
+        wi[j & 1][wave] = c0 + (second ? 1 : 0);
+      }
     }
     // (LDS-only barriers: the R rows this kernel stores are read by later
     // launches only, and waiting for their acknowledgement at every pivot
@@ -196,80 +288,86 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
     // candidate; the largest value wins, ties to the lowest wave (whose
     // columns are the lower ones)
     const double cv = lane < nwaves ? wv[j & 1][lane] : -INFINITY;
-    const int ci = lane < nwaves ? wi[j & 1][lane] : 0x7fffffff;
-    const double bmax = max8_f64(cv);
-    const uint64_t bhit = __ballot(lane < 8 && cv == bmax);
-    const int bw = bhit != 0 ? (__ffsll((unsigned long long)bhit) - 1) : 0;
-    const double pv = bhit != 0 ? bmax : -INFINITY;
+    const int ci = lane < nwaves ? wi[j & 1][lane] : 0;
+    uint64_t hit;
+    {
+      const int key = __double2hiint(cv);
+      const int top = max8_i32(key);  // (all lanes active: DPP)
+      hit = __ballot(lane < nwaves && key == top);
+      if ((hit & (hit - 1)) != 0) {
+        const double x = (hit >> lane) & 1 ? cv : -INFINITY;
+        const double m = max8_f64(x);
+        hit = __ballot(lane < nwaves && x == m);
+      }
+    }
+    const int bw = hit != 0 ? __builtin_ctzll(hit) : 0;
+    const double pv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(cv), bw),
+                                       __builtin_amdgcn_readlane(__double2loint(cv), bw));
     const int p = __builtin_amdgcn_readlane(ci, bw);
-    if (j == 0 && J0 == 0 && ref_r00 == nullptr) {
+    if (j == 0 && Ji == 0 && ref_r00 == nullptr) {
       r00 = pv > 0.0 ? sqrt(pv) : 0.0;
       zr2 = (zeta * r00) * (zeta * r00);
     }
-    if (!(pv > 0.0) || !(pv > zr2)) {
-      stop = true;
-      active = false;
-      continue;
-    }
-    // prefetch the pivot row of the Schur complement (symmetric: = column p)
-    double s_pc[2];
+    if (!(pv > 0.0) || !(pv > zr2)) return false;
+    // the pivot row of the Schur complement (symmetric: = column p) and the
+    // column's entries of the panel so far
+    const double s0 = S[p * di + q0], s1 = S[p * di + q1];
+    double blo = 0.0, bhi = 0.0;
+    if constexpr (SH == NB) {
+      if (j > 0) blo = rc[p * rc_stride(SH) + (lane & 15)];
+      if (j > 16) bhi = rc[p * rc_stride(SH) + 16 + (lane & 15)];
+    } else {
+      if (j > 0 && j <= 16) blo = rc[p * rc_stride(SH) + (lane & 15)];
+      if (j > 16) {
+        bhi = rc[p * rc_stride(SH) + (lane & 15)];
+        if ((p >> 1) == tid) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) s_pc[q] = (c0 + q < di) ? S[p * di + c0 + q] : 0.0;
-    if ((p >> 1) == tid) {
-#pragma unroll
-      for (int t = 0; t < j; ++t) bc[t] = (p & 1) ? rp1[t] : rp0[t];
+          for (int t = 0; t < 16; ++t) post[t] = (p & 1) ? rp1[t] : rp0[t];
+        }
+        lds_barrier();
+        blo = post[lane & 15];
+      }
     }
-    lds_barrier();
-    // rjj and 1 / rjj (the reciprocal estimate and two Newton steps: rjj is
-    // positive, finite and normal here, so the scaled division's special
-    // cases do not arise) while the column's entries are read and summed
-    const double rjj = sqrt(pv);
-    double inv = __builtin_amdgcn_rcp(rjj);
-    inv = fma(inv, fma(-rjj, inv, 1.0), inv);
-    inv = fma(inv, fma(-rjj, inv, 1.0), inv);
-    double acc0 = s_pc[0], acc1 = s_pc[1];
-#pragma unroll
-    for (int t = 0; t < j; ++t) {
-      const double b = bc[t];
-      acc0 = fma(-b, rp0[t], acc0);
-      acc1 = fma(-b, rp1[t], acc1);
-    }
+    double inv, rjj;
+    rsqrt_sqrt(pv, &inv, &rjj);
+    double acc0 = 0.0, acc1 = 0.0;
+    fma_rows<j>(acc0, acc1, blo, bhi, rp0, rp1);
     // selects, not branches: the pivot column takes rjj and leaves the
     // candidates, live columns take their entry and downdate their diagonal,
     // dead ones (and those past d) take 0
-    double val[2] = {acc0 * inv, acc1 * inv};
+    double val[2] = {(s0 + acc0) * inv, (s1 + acc1) * inv};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const bool piv = c0 + q == p;
-      const double nd = fma(-val[q], val[q], dg[q]);
-      val[q] = piv ? rjj : (alive[q] ? val[q] : 0.0);
-      dg[q] = piv ? -INFINITY : (alive[q] ? nd : dg[q]);
-      alive[q] = alive[q] && !piv;
+      const double nd = fmax(fma(-val[q], val[q], dg[q]), -INFINITY);  // (-inf stays, a NaN leaves)
+      val[q] = piv ? rjj : (dg[q] != -INFINITY ? val[q] : 0.0);
+      dg[q] = piv ? -INFINITY : nd;
     }
     rp0[j] = val[0];
     rp1[j] = val[1];
-    if (c0 + 1 < d && ((d & 1) == 0)) {  // the pair is 16-byte aligned (d even, c0 even)
+    if (c0 < di) rc[c0 * rc_stride(SH) + j % SH] = val[0];
+    if (c0 + 1 < di) rc[(c0 + 1) * rc_stride(SH) + j % SH] = val[1];
+    double* rrow = st.Rrows + J * di + c0;
+    if (pair) {
       *reinterpret_cast<double2*>(rrow) = make_double2(val[0], val[1]);
     } else {
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        if (c0 + q < d) rrow[q] = val[q];
+      if (c0 < di) rrow[0] = val[0];
+      if (c0 + 1 < di) rrow[1] = val[1];
     }
-    rrow += d;
-    if (tid == 0) st.piv[J] = p;
+    mine = lane == j ? p : mine;
     ++J;
-  }
+    return true;
+  });
 
 #pragma unroll
   for (int q = 0; q < 2; ++q)
-    if (c0 + q < d) st.diag[c0 + q] = dg[q];
+    if (c0 + q < di) st.diag[c0 + q] = dg[q];
+  if (tid < J - Ji) st.piv[Ji + tid] = mine;
   if (tid == 0) {
     *st.r00 = r00;
-    st.flags[1] = (int32_t)J;
-    if (stop || J >= d) {
-      st.flags[0] = 1;
-      *rank_out = J;
-    }
+    st.flags[0] = (!whole || J >= di) ? 1 : 0;
+    st.flags[1] = J;
+    if (!whole || J >= di) *rank_out = J;
   }
 }
 
@@ -577,17 +675,6 @@ __global__ __launch_bounds__(768) void pivchol_small_kernel(const double* __rest
   }
 }
 
-// 1 / sqrt(x) (hardware estimate and two Newton steps) and sqrt(x) from it
-// with one correction step; x positive, finite and normal.
-__device__ __forceinline__ void rsqrt_sqrt(double x, double* inv, double* root) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = y * fma(-0.5 * x * y, y, 1.5);
-  y = y * fma(-0.5 * x * y, y, 1.5);
-  const double r = x * y;
-  *root = fma(fma(-r, r, x), 0.5 * y, r);
-  *inv = y;
-}
-
 // ---------------------------------------------------------------------------
 // d <= 64: the whole factorisation by one wave, lane c owning column c, with
 // the Gram and R in LDS (no barrier in the pivot loop, no global memory read
@@ -841,15 +928,16 @@ hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState&
     pivchol_small_kernel<<<1, 64 * waves, 0, s>>>(B, (int)d, zeta, st, rank_out, fixed, ref_r00);
     return launch_pivchol_finalize(d, st, rank_out, perm_out, R_out, s);
   }
-  // the panels track their progress in flags
-  hipError_t e = launch_fill_zero(st.flags, 64 * sizeof(int32_t), s);
-  if (e != hipSuccess) return e;
   const int threads = (int)(((d + 64 * kPanelCols - 1) / (64 * kPanelCols)) * 64);
+  const bool all = d <= kShareD;
+  auto panel = all ? (fixed ? pivchol_panel_kernel<true, NB> : pivchol_panel_kernel<false, NB>)
+                   : (fixed ? pivchol_panel_kernel<true, 16> : pivchol_panel_kernel<false, 16>);
+  const size_t lds = sizeof(double) * (size_t)d * (all ? rc_stride(NB) : rc_stride(16));
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(panel),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
   for (int64_t J0 = 0; J0 < d; J0 += NB) {
-    if (fixed)
-      pivchol_panel_kernel<true><<<1, threads, 0, s>>>(B, d, zeta, J0, st, rank_out, ref_r00);
-    else
-      pivchol_panel_kernel<false><<<1, threads, 0, s>>>(B, d, zeta, J0, st, rank_out, ref_r00);
+    panel<<<1, threads, lds, s>>>(B, d, zeta, J0, st, rank_out, ref_r00);
     if (J0 + NB < d) {
       // S <- S - R_panel^T R_panel over the panel's NB rows (skipped once done)
       const double* Rp = st.Rrows + J0 * d;
