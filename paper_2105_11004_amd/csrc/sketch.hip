@@ -323,26 +323,30 @@ hipError_t launch_dense_typed(const void* A, int64_t n, int64_t d, int64_t ld, c
 // Same bucket-major gather as the dense kernel.  A wave takes the staged
 // row list 64 entries at a time (lane j <-> entry j: its row's extent from
 // row_ptr), then walks those rows U at a time: the first 64 nonzeros of U
-// rows are loaded together (lane t <-> nonzero t of a row) and then added,
-// row after row, into the wave's private FP64 accumulator in LDS with
-// ds_add_f64.  Within one row the column ids are distinct, so one add
-// instruction never hits an address twice, and the adds of one wave execute
-// in program order: the accumulation order is a fixed function of the input
-// and S A is bitwise reproducible.  The four wave accumulators are summed in
-// a fixed order at the end.
-template <typename T>
-__device__ __forceinline__ double load_as_double(const T* p);
-template <>
-__device__ __forceinline__ double load_as_double<double>(const double* p) { return *p; }
-template <>
-__device__ __forceinline__ double load_as_double<float>(const float* p) { return (double)*p; }
-template <>
-__device__ __forceinline__ double load_as_double<__hip_bfloat16>(const __hip_bfloat16* p) {
-  const uint16_t bits = *reinterpret_cast<const uint16_t*>(p);
-  return (double)__uint_as_float((uint32_t)bits << 16);
+// rows are loaded together (lane t <-> nonzero t of a row), the next U rows'
+// loads are issued, and the first ones are added, row after row, into the
+// wave's private FP64 accumulator in LDS with ds_add_f64; what rows have
+// beyond 64 follows, row by row.  Within one row the column ids are distinct,
+// so one add instruction never hits an address twice, and the adds of one
+// wave execute in program order: the accumulation order is a fixed function
+// of the input and S A is bitwise reproducible.  The four wave accumulators
+// are summed in a fixed order at the end.
+//
+// Bound by the gather: a bucket's rows lie anywhere in A, so each costs whole
+// 64-byte lines of row_ptr, col_idx and vals (2.1 GB for the 1.2 GB of 2^23 x
+// 512 at 16 nonzeros a row), beside a row's ~20 vector instructions (half of
+// the issue slots).  No load may wait for another: with a conversion or a
+// select next to it under `if (lane < length)` the compiler waited for every
+// load in turn and the pass took 1332 us; all loads unconditional, 747;
+// and the next U rows in flight while these are added, 675.  More waves (64
+// registers) and the rows of a bucket in ascending windows changed nothing.
+__device__ __forceinline__ double to_double(double x) { return x; }
+__device__ __forceinline__ double to_double(float x) { return (double)x; }
+__device__ __forceinline__ double to_double(__hip_bfloat16 x) {
+  return (double)__uint_as_float((uint32_t)__builtin_bit_cast(uint16_t, x) << 16);
 }
 
-constexpr int kCsrU = 8;  // rows whose first 64 nonzeros are in flight together
+constexpr int kCsrU = 8;  // rows whose first 64 nonzeros are loaded together
 
 template <typename T>
 __global__ __launch_bounds__(kThreads) void countsketch_csr_kernel(const T* __restrict__ vals,
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(kThreads) void countsketch_csr_kernel(const T* __re
   for (int64_t c = threadIdx.x; c < kWaves * d; c += kThreads) acc[c] = 0.0;
   side_draw(g);
 
-  const int64_t T_b = bucket_len(hp, b);
+  const int64_t T_b = nnz > 0 ? bucket_len(hp, b) : 0;
   const uint64_t i0 = T_b > 0 ? bucket_start(hp, b) : 0;
   for (int64_t t0 = 0; t0 < T_b; t0 += kChunk) {
     const int cnt = (int)min<int64_t>(kChunk, T_b - t0);
@@ -375,69 +379,88 @@ __global__ __launch_bounds__(kThreads) void countsketch_csr_kernel(const T* __re
       const int q = q0 + lane;
       const uint32_t ent = q < cnt ? entries[q] : kInvalid;
       int64_t start = 0;
-      int len = 0;
-      int neg = 0;
+      uint32_t len = 0;  // with the sign in bit 31
       if (ent != kInvalid) {
         const int64_t row = (int64_t)(ent & 0x7FFFFFFFu);
         // a well-formed row lies in [0, nnz) and has at most d nonzeros; the
         // clamps keep a malformed row_ptr from reading out of bounds
         start = min(max(row_ptr[row], (int64_t)0), nnz);
         const int64_t end = min(max(row_ptr[row + 1], start), nnz);
-        len = (int)min<int64_t>(end - start, d);
-        neg = (ent >> 31) != 0;
+        len = (uint32_t)min<int64_t>(end - start, d);
       }
-      const int rows_here = min(64, cnt - q0);
-      for (int g = 0; g < rows_here; g += kCsrU) {
-        int32_t cv[kCsrU];
-        double xv[kCsrU];
-        int64_t st[kCsrU];
-        int ln[kCsrU];
+      if (len == 0) start = 0;  // (an empty row's lanes load element 0)
+      uint64_t longer = __ballot(len > 64);
+      len |= ent & 0x80000000u;
+      int32_t cv[2][kCsrU];
+      T xv[2][kCsrU];
+      uint32_t sl[2][kCsrU];  // the row's length and sign (uniform)
+      auto at = [&](int j) -> int64_t {
+        return ((int64_t)__builtin_amdgcn_readlane((int)(start >> 32), j) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane((int)start, j);
+      };
+      // rows g .. g + kCsrU - 1 of the slice, every load unconditional (lanes
+      // past a row's end take its first nonzero)
+      auto load = [&](auto set, int g) {
+        constexpr int S = decltype(set)::value;
 #pragma unroll
         for (int u = 0; u < kCsrU; ++u) {
-          const int j = g + u;  // uniform
-          const int jj = j < 64 ? j : 63;
-          st[u] = ((int64_t)__builtin_amdgcn_readlane((int)(start >> 32), jj) << 32) |
-                  (uint32_t)__builtin_amdgcn_readlane((int)start, jj);
-          ln[u] = j < rows_here ? __builtin_amdgcn_readlane(len, jj) : 0;
-          const int sg = __builtin_amdgcn_readlane(neg, jj);
-          cv[u] = 0;
-          xv[u] = 0.0;
-          if (lane < ln[u]) {
-            cv[u] = col_idx[st[u] + lane];
-            const double x = load_as_double<T>(vals + st[u] + lane);
-            xv[u] = sg ? -x : x;
-          }
+          const int j = (g + u) & 63;
+          const int64_t st = at(j);
+          sl[S][u] = (uint32_t)__builtin_amdgcn_readlane((int)len, j);
+          const uint32_t t = (uint32_t)lane < (sl[S][u] & 0x7FFFFFFFu) ? lane : 0;
+          cv[S][u] = (col_idx + st)[t];
+          xv[S][u] = (vals + st)[t];
         }
+        asm volatile("" ::: "memory");  // keeps a load from sinking into its add's branch
+      };
+      auto add_one = [&](T v, int32_t c, bool in, uint32_t sign) {
+        const double x = to_double(v);
+        const double sx = __hiloint2double(__double2hiint(x) ^ (int)(sign & 0x80000000u), __double2loint(x));
+        if (in && (uint32_t)c < (uint32_t)d)
+          __hip_atomic_fetch_add(my + c, sx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      };
+      auto add = [&](auto set) {
+        constexpr int S = decltype(set)::value;
 #pragma unroll
-        for (int u = 0; u < kCsrU; ++u) {
-          if (lane < ln[u] && (uint32_t)cv[u] < (uint32_t)d)
-            __hip_atomic_fetch_add(my + cv[u], xv[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int u = 0; u < kCsrU; ++u)
+          add_one(xv[S][u], cv[S][u], (uint32_t)lane < (sl[S][u] & 0x7FFFFFFFu), sl[S][u]);
+      };
+      const std::integral_constant<int, 0> s0;
+      const std::integral_constant<int, 1> s1;
+      const int rows = min(64, cnt - q0);
+      load(s0, 0);
+      for (int g = 0;; g += 2 * kCsrU) {
+        if (g + kCsrU >= rows) {
+          add(s0);
+          break;
         }
-        // nonzeros beyond the first 64 of a row: row by row, up to 8 chunks
-        // of 64 loaded together before they are added
+        load(s1, g + kCsrU);
+        add(s0);
+        if (g + 2 * kCsrU >= rows) {
+          add(s1);
+          break;
+        }
+        load(s0, g + 2 * kCsrU);
+        add(s1);
+      }
+      // nonzeros beyond the first 64 of a row: row by row, eight pieces of 64
+      // loaded together before they are added
+      for (; longer != 0; longer &= longer - 1) {
+        const int j = __builtin_ctzll(longer);
+        const int64_t st = at(j);
+        const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)len, j);
+        const int ln = (int)(l & 0x7FFFFFFFu);
+        for (int off0 = 64; off0 < ln; off0 += 8 * 64) {
 #pragma unroll
-        for (int u = 0; u < kCsrU; ++u) {
-          const int sg = __builtin_amdgcn_readlane(neg, (g + u) < 64 ? g + u : 63);
-          for (int off0 = 64; off0 < ln[u]; off0 += 8 * 64) {
-            int32_t c8[8];
-            double x8[8];
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-              const int off = off0 + 64 * v + lane;
-              c8[v] = 0;
-              x8[v] = 0.0;
-              if (off < ln[u]) {
-                c8[v] = col_idx[st[u] + off];
-                const double x = load_as_double<T>(vals + st[u] + off);
-                x8[v] = sg ? -x : x;
-              }
-            }
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-              if (off0 + 64 * v + lane < ln[u] && (uint32_t)c8[v] < (uint32_t)d)
-                __hip_atomic_fetch_add(my + c8[v], x8[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
+          for (int v = 0; v < 8; ++v) {
+            const int off = off0 + 64 * v + lane;
+            const uint32_t t = off < ln ? off : 0;
+            cv[0][v] = (col_idx + st)[t];
+            xv[0][v] = (vals + st)[t];
           }
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int v = 0; v < 8; ++v) add_one(xv[0][v], cv[0][v], off0 + 64 * v + lane < ln, l);
         }
       }
     }
