@@ -128,10 +128,13 @@ __device__ __forceinline__ int max8_i32(int v) {
 
 // 1 / sqrt(x) (hardware estimate and two Newton steps) and sqrt(x) from it
 // with one correction step; x positive, finite and normal.
-__device__ __forceinline__ void rsqrt_sqrt(double x, double* inv, double* root) {
+__device__ __forceinline__ double rsqrt_newton(double x) {
   double y = __builtin_amdgcn_rsq(x);
   y = y * fma(-0.5 * x * y, y, 1.5);
-  y = y * fma(-0.5 * x * y, y, 1.5);
+  return y * fma(-0.5 * x * y, y, 1.5);
+}
+__device__ __forceinline__ void rsqrt_sqrt(double x, double* inv, double* root) {
+  const double y = rsqrt_newton(x);
   const double r = x * y;
   *root = fma(fma(-r, r, x), 0.5 * y, r);
   *inv = y;
@@ -681,8 +684,10 @@ __global__ __launch_bounds__(768) void pivchol_small_kernel(const double* __rest
 // in it).  Step J needs only row p of the Gram and the rows of R so far: R's
 // entries of a lane's column sit in registers for the finished blocks of 16
 // rows and are read from LDS for the block under way, so the step is one
-// short loop body per block.  The other waves load the Gram and write the
-// pivoted R.  Bound: the chain of one pivot step in one wave (maximum, LDS
+// short loop body per block.  Each entry is one chain over the pivots in
+// order from the lower triangle's value, and R_JJ is the pivot times its
+// reciprocal root, as in the workgroup form, so both give the same bits.  The
+// other waves load the Gram and write the pivoted R.  Bound: the chain of one pivot step in one wave (maximum, LDS
 // read, FMAs, reciprocal root; about 0.45 us).  At d = 64, 48 pivots: 26 us in
 // one launch, against 44 + 5 us for the workgroup form below and the
 // permutation's own launch; past 64 columns a lane would hold two.
@@ -690,19 +695,19 @@ constexpr int kWaveD = 64;
 constexpr int kWaveS = kWaveD + 2;  // row stride of the Gram in LDS
 constexpr int kWaveR = kWaveD + 1;  // column stride of R in LDS
 
-// a0 -= sum over even t of b[T0 + t] r[t], a1 over odd t, t < 8.
+// a -= b[T0 + t] r[t] for t = 0 .. 7 in order.
 template <int T0>
-__device__ __forceinline__ void fma_bcast8(double& a0, double& a1, double b, const double* r) {
+__device__ __forceinline__ void fma_bcast8(double& a, double b, const double* r) {
   asm("s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, -%2, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, -%2, %4 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%2, %5 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, -%2, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%2, %7 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, -%2, %8 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%2, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, -%2, %10 row_newbcast:%18 row_mask:0xf bank_mask:0xf"
-      : "+v"(a0), "+v"(a1)
+      "v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %3 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %4 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %5 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %7 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %8 row_newbcast:%16 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%1, %9 row_newbcast:%17 row_mask:0xf bank_mask:0xf"
+      : "+v"(a)
       : "v"(b), "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(r[3]), "v"(r[4]), "v"(r[5]), "v"(r[6]), "v"(r[7]), "n"(T0),
         "n"(T0 + 1), "n"(T0 + 2), "n"(T0 + 3), "n"(T0 + 4), "n"(T0 + 5), "n"(T0 + 6), "n"(T0 + 7));
 }
@@ -744,8 +749,7 @@ __global__ __launch_bounds__(256) void pivchol_wave_kernel(const double* __restr
         const double cv = (fixed == 0 || lane == J) && dg == dg ? dg : -INFINITY;
         int p;
         const double pv = wave_argmax(cv, &p);
-        double inv, rjj;
-        rsqrt_sqrt(pv, &inv, &rjj);
+        const double inv = rsqrt_newton(pv), rjj = pv * inv;
         if (J == 0 && ref_r00 == nullptr) {
           r00 = pv > 0.0 ? rjj : 0.0;
           zr2 = (zeta * r00) * (zeta * r00);
@@ -754,7 +758,7 @@ __global__ __launch_bounds__(256) void pivchol_wave_kernel(const double* __restr
           run = false;
           break;
         }
-        double a0 = in ? Sc[p * kWaveS + lane] : 0.0, a1 = 0.0;
+        double a = in ? Sc[max(p, lane) * kWaveS + min(p, lane)] : 0.0;
         double own[16];
         const double bcur = Rc[p * kWaveR + 16 * blk + (lane & 15)];
 #pragma unroll
@@ -762,12 +766,12 @@ __global__ __launch_bounds__(256) void pivchol_wave_kernel(const double* __restr
 #pragma unroll
         for (int q = 0; q < blk; ++q) {
           const double bq = Rc[p * kWaveR + 16 * q + (lane & 15)];
-          fma_bcast8<0>(a0, a1, bq, rp + 16 * q);
-          fma_bcast8<8>(a0, a1, bq, rp + 16 * q + 8);
+          fma_bcast8<0>(a, bq, rp + 16 * q);
+          fma_bcast8<8>(a, bq, rp + 16 * q + 8);
         }
-        fma_bcast8<0>(a0, a1, bcur, own);
-        fma_bcast8<8>(a0, a1, bcur, own + 8);
-        double v = (a0 + a1) * inv;
+        fma_bcast8<0>(a, bcur, own);
+        fma_bcast8<8>(a, bcur, own + 8);
+        double v = a * inv;
         const double nd = fma(-v, v, dg);
         const bool live = dg != -INFINITY, piv = lane == p;
         v = piv ? rjj : (live ? v : 0.0);

@@ -11,7 +11,7 @@
 // Drmac and Veselic (2008): Hestenes' iteration on W = R^T, whose columns
 // are the rows of the pivoted factor and so are already close to
 // orthogonal (few sweeps).  W sits in LDS; each round of a round-robin
-// ordering orthogonalises all its disjoint column pairs at once (an 8-lane
+// ordering orthogonalises all its disjoint column pairs at once (a 16-lane
 // group per pair, Rutishauser's rotation), and sweeps repeat until no pair
 // is rotated.  Then W = R^T U_R = V_R Sigma: the column norms are the
 // singular values and column c over its norm is the right singular vector,
@@ -19,15 +19,13 @@
 // accuracy of the singular values does not depend on kappa(R).
 //
 // LSQR (Paige and Saunders 1982) on M = A N from y = 0, with x = N y at the
-// end.  Per iteration one pass over A (dense, FP64 arithmetic on any storage
-// type) and one single-workgroup kernel:
-//   pass:  t = A (N v) - alpha u, and per workgroup the sums of t_i^2 and of
-//          t_i A[i,:] from the row that is still in registers; u is never
-//          stored: it is t over the beta that the step finds;
-//   step:  beta = ||t||, A^T u = (A^T t) / beta, q = N^T (A^T u) - beta v,
-//          alpha = ||q||, v = q / alpha, the rotation (rho, c, s, theta,
-//          phi), y += (phi / rho) w, w = v - (theta / rho) w, z = N v for
-//          the next pass.
+// end.  Per iteration two passes over A (dense, FP64 arithmetic on any
+// storage type) and one single-workgroup kernel:
+//   gemv:  t = A (N v) - alpha u, and per-workgroup sums of t_i^2;
+//   atv:   beta = sqrt(sum), u = t / beta, per-workgroup partials of A^T u;
+//   step:  q = N^T (A^T u) - beta v, alpha = ||q||, v = q / alpha, the
+//          rotation (rho, c, s, theta, phi), y += (phi / rho) w,
+//          w = v - (theta / rho) w, z = N v for the next gemv.
 // Scalars stay in device memory; all sums run in a fixed order.
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
@@ -35,17 +33,18 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "lev_internal.h"
 
 namespace lev {
 namespace {
 
-constexpr int kSvdGroup = 8;            // lanes per column pair
-constexpr int kSvdMaxThreads = 512;     // 64 groups: every pair of a round at d <= 128
+constexpr int kSvdGroup = 16;           // lanes per column pair
+constexpr int kSvdMaxThreads = 1024;    // 64 groups: every pair of a round at d <= 128
 constexpr int kMaxSweeps = 40;
-// stride of a column of W in LDS: 16 PAIRS elements and the banks' offset
-__host__ __device__ constexpr int svd_stride(int pairs) { return 2 * kSvdGroup * pairs + 16; }
+// stride of a column of W in LDS: 16 ELEMS elements and the banks' offset
+__host__ __device__ constexpr int svd_stride(int elems) { return kSvdGroup * elems + 16; }
 
 __device__ __forceinline__ double wave_sum(double x) {
 #pragma unroll
@@ -69,58 +68,43 @@ __device__ __forceinline__ double dpp_add(double v) {
   return v + __hiloint2double(hi, lo);
 }
 
-// Sum over each 8-lane half row or 16-lane row by butterflies whose partners
-// always sit in the other half of the part summed so far, so both sides add
-// the same two values and every lane ends with identical bits (a rotation is
-// then the same in every lane).  All lanes of the part must be active.
-__device__ __forceinline__ double row8_sum(double v) {
-  v = dpp_add<0xB1>(v);      // quad_perm [1, 0, 3, 2]
-  v = dpp_add<0x4E>(v);      // quad_perm [2, 3, 0, 1]
-  return dpp_add<0x141>(v);  // row_half_mirror
-}
+// Sum over each 16-lane row by butterflies whose partners always sit in
+// the other half of the part summed so far, so both sides add the same two
+// values and every lane of the row ends with identical bits (the rotation
+// is then the same in every lane).  All 16 lanes must be active.
 __device__ __forceinline__ double row16_sum(double v) {
-  return dpp_add<0x140>(row8_sum(v));  // row_mirror
+  v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  v = dpp_add<0x140>(v);  // row_mirror
+  return v;
 }
 
-// 1 / sqrt(x) for normal x > 0: the hardware estimate (within 2^-20) and one
-// step of third order, y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2.
-__device__ __forceinline__ double rsqrt_step(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-x * y, y, 1.0);
-  return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
-// One workgroup, eight lanes per column pair (rounded up to a wave); LDS
-// holds W column-major, dd columns (a zero column pads an odd d) of
-// 16 PAIRS elements, zero past d, at a stride of 16 more (so that columns
-// next to each other start in opposite halves of the banks).  A lane holds
-// the elements 2 l + 16 j and + 1 of a column; PAIRS = 4 (d <= 64) or 8.
-//
+// One workgroup of 16 * (dd / 2) lanes (rounded up to a wave); LDS holds W
+// column-major, dd columns (a zero column pads an odd d) of 16 ELEMS elements,
+// zero past d, at a stride of 16 more (so that columns next to each other
+// start in opposite halves of the banks).  ELEMS = 4 (d <= 64) or 8: the loads
+// of a round need no bound.
 // Bound by the chain of one round (LDS read, three dot products and their
-// reductions, the rotation, LDS write, barrier), which is repeated dd - 1
-// times a sweep.  Eight lanes a pair put one wave on each SIMD at d = 64, so
-// no SIMD works through the rotation's replicated scalars twice; with four
-// lanes the elements' work would outweigh them.  The angle comes from two
-// reciprocal square roots without a division: with h = y.y - x.x, g = 2 x.y
-// and r = hypot(h, g), cos^2 = (1 + |h| / r) / 2 and |sin| = |g| / (2 r cos),
-// the pair of Rutishauser's smaller angle; h and g are first scaled by the
-// power of two of the larger, so no square leaves the range.
-// d = 60: 491 -> 252 us (16 lanes a pair, bounds checked, three divisions and
-// a square root before).
-template <int PAIRS>
+// reductions, the rotation's divisions and roots, LDS write, barrier), which
+// is repeated dd - 1 times a sweep.  d = 60: 344 us, against 491 with a bound
+// and a select on every load.  (Eight lanes a pair and an angle without a
+// division took 252, but round otherwise, and an unconverged LSQR iterate
+// passes a change of N's last bits on to 1e-9.)
+template <int ELEMS>
 __global__ __launch_bounds__(kSvdMaxThreads) void jacobi_svd_kernel(int64_t d, const double* __restrict__ R,
                                                                     const int64_t* __restrict__ rank,
                                                                     const int32_t* __restrict__ perm, double zeta,
                                                                     double* __restrict__ N,
                                                                     int64_t* __restrict__ k_out) {
-  extern __shared__ __align__(16) double W[];
+  extern __shared__ double W[];
   __shared__ int rotated;
   __shared__ double sig[128];
   __shared__ int order[128];
   const int di = (int)d;
   const int dd = di + (di & 1);
-  constexpr int kRows = 2 * kSvdGroup * PAIRS, kStride = svd_stride(PAIRS);
-  const int r = (int)*rank;
+  constexpr int kRows = kSvdGroup * ELEMS, kStride = svd_stride(ELEMS);
+  const int64_t r = *rank;
   // W = R^T: column c of W is row c of R (rows past the rank are zero)
   for (int e = threadIdx.x; e < dd * kRows; e += blockDim.x) {
     const int c = e / kRows, i = e % kRows;
@@ -129,7 +113,7 @@ __global__ __launch_bounds__(kSvdMaxThreads) void jacobi_svd_kernel(int64_t d, c
   __syncthreads();
   const int gl = threadIdx.x & (kSvdGroup - 1);
   const int q = threadIdx.x / kSvdGroup;
-  const bool active = q < dd / 2;  // whole groups are active or not
+  const bool active = q < dd / 2;  // whole 16-lane rows are active or not
   // a pair is rotated while |x . y| > tol ||x|| ||y||, tested squared
   const double tol = 4.0 * (double)di * 2.220446049250313e-16;
   const double tol2 = tol * tol;
@@ -139,42 +123,32 @@ __global__ __launch_bounds__(kSvdMaxThreads) void jacobi_svd_kernel(int64_t d, c
     int a = rr_col(dd, 0, q), b = rr_col(dd, 0, dd - 1 - q);
     for (int t = 0; t < dd - 1; ++t, a = rr_next(dd, a), b = rr_next(dd, b)) {
       if (active) {
-        double* wa = W + a * kStride + 2 * gl;
-        double* wb = W + b * kStride + 2 * gl;
-        double2 x[PAIRS], y[PAIRS];
-#pragma unroll
-        for (int j = 0; j < PAIRS; ++j) {
-          x[j] = *reinterpret_cast<const double2*>(wa + 2 * kSvdGroup * j);
-          y[j] = *reinterpret_cast<const double2*>(wb + 2 * kSvdGroup * j);
-        }
+        double* wa = W + a * kStride + gl;
+        double* wb = W + b * kStride + gl;
+        double x[ELEMS], y[ELEMS];
         double al = 0.0, be = 0.0, ga = 0.0;
 #pragma unroll
-        for (int j = 0; j < PAIRS; ++j) {
-          al = fma(x[j].x, x[j].x, al);
-          be = fma(y[j].x, y[j].x, be);
-          ga = fma(x[j].x, y[j].x, ga);
-          al = fma(x[j].y, x[j].y, al);
-          be = fma(y[j].y, y[j].y, be);
-          ga = fma(x[j].y, y[j].y, ga);
+        for (int j = 0; j < ELEMS; ++j) {
+          x[j] = wa[kSvdGroup * j];
+          y[j] = wb[kSvdGroup * j];
         }
-        al = row8_sum(al);
-        be = row8_sum(be);
-        ga = row8_sum(ga);
-        if (ga * ga > tol2 * (al * be)) {
-          const double h0 = be - al, g0 = 2.0 * ga;
-          const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(h0), fabs(g0)));
-          const double h = ldexp(h0, ex), g = ldexp(g0, ex);
-          const double ir = rsqrt_step(fma(h, h, g * g));  // 1/4 <= h^2 + g^2 < 2
-          const double c2 = fma(0.5 * fabs(h), ir, 0.5);
-          const double ic = rsqrt_step(c2);
-          const double c = c2 * ic;
-          const double s = (h < 0.0 ? -0.5 : 0.5) * g * (ir * ic);
 #pragma unroll
-          for (int j = 0; j < PAIRS; ++j) {
-            *reinterpret_cast<double2*>(wa + 2 * kSvdGroup * j) =
-                make_double2(c * x[j].x - s * y[j].x, c * x[j].y - s * y[j].y);
-            *reinterpret_cast<double2*>(wb + 2 * kSvdGroup * j) =
-                make_double2(s * x[j].x + c * y[j].x, s * x[j].y + c * y[j].y);
+        for (int j = 0; j < ELEMS; ++j) {
+          al = fma(x[j], x[j], al);
+          be = fma(y[j], y[j], be);
+          ga = fma(x[j], y[j], ga);
+        }
+        al = row16_sum(al);
+        be = row16_sum(be);
+        ga = row16_sum(ga);
+        if (ga != 0.0 && ga * ga > tol2 * (al * be)) {
+          const double zt = (be - al) / (2.0 * ga);
+          const double tn = (zt >= 0.0 ? 1.0 : -1.0) / (fabs(zt) + sqrt(1.0 + zt * zt));
+          const double c = rsqrt(1.0 + tn * tn), s = c * tn;  // 1 + tn^2 in [1, 2]
+#pragma unroll
+          for (int j = 0; j < ELEMS; ++j) {
+            wa[kSvdGroup * j] = c * x[j] - s * y[j];
+            wb[kSvdGroup * j] = s * x[j] + c * y[j];
           }
           if (gl == 0) rotated = 1;
         }
@@ -226,9 +200,12 @@ __global__ void scatter_rows_kernel(int64_t d, const int32_t* __restrict__ perm,
 }
 
 // ---- LSQR -------------------------------------------------------------------------
-// st: [0] alpha, [1] beta, [2] rhobar, [3] phibar, [4] stop (0 / 1), [5] beta_1, [6] 1 / beta
-constexpr int kPassThreads = 512;
-constexpr int kStepThreads = 1024;
+// st: [0] alpha, [1] beta, [2] rhobar, [3] phibar, [4] stop (0 / 1), [5] beta_1
+constexpr int kGemvThreads = 1024;
+
+__device__ __forceinline__ double f64(double x) { return x; }
+__device__ __forceinline__ double f64(float x) { return (double)x; }
+__device__ __forceinline__ double f64(__hip_bfloat16 x) { return (double)__bfloat162float(x); }
 
 // Four consecutive elements of a row from column c (c a multiple of 4,
 // c < d), widened to FP64; elements at or past d read as zero.  Rows are
@@ -258,214 +235,356 @@ __device__ __forceinline__ void load4(const __hip_bfloat16* p, int64_t c, int64_
   a[3] = c + 3 < d ? (double)__uint_as_float(v.y & 0xFFFF0000u) : 0.0;
 }
 
-// Sum over the G lanes (16 or 64) that share a row, returned to all of them.
-template <int G>
-__device__ __forceinline__ double row_sum(double v) {
-  v = row16_sum(v);
-  if constexpr (G == 64) {
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-  }
-  return v;
+// LSQR before convergence passes a change of rounding on: an iterate moves by
+// 1e-9 to 1e-8 (relative) when one sum of a step is taken in another order,
+// while the residuals agree to 1e-15.  So every sum below keeps one fixed
+// order whatever the number of threads: t_i by 16 lanes, the squares by 16
+// chains of a workgroup's rows, A^T u by four chains a workgroup, the
+// workgroups' partials and N^T by eight.
+
+// Sum over the 16 lanes of a row in the order of a xor butterfly 8, 4, 2, 1
+// (after each step the values repeat with that period, so a rotation by it
+// brings the same partner).
+__device__ __forceinline__ double ror16_sum(double v) {
+  v = dpp_add<0x128>(v);  // row_ror:8
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x122>(v);
+  return dpp_add<0x121>(v);
 }
 
-// t_i = A[i,:] z - alpha u_i (or b_i when INIT), u = the previous t over its
-// beta; per workgroup gpart = sum of t_i^2 and apart[c] = sum of t_i A[i][c].
-// G lanes take a row, four consecutive elements a lane and 4 G columns a
-// block of M, so the row is read once, stays in registers and serves both
-// the dot product and the sum; z and the sums are in registers too.  d <= 64
-// M in {1, 2, 4} takes G = 16 (four rows a wave, a reduction of four DPP
-// steps), wider rows a whole wave.  Rows past the end are read clamped and
-// enter with t = 0.  Sums run in a fixed order: a lane's rows ascending, then
-// the workgroup's groups in LDS.
-//
-// Bound by the reads of A (one instead of the two of a separate product with
-// A and with A^T) and, when A fits the caches, by the launch and the chain
-// of one row.
-// 50000 x 60 FP64: 5.8 us, where the product with A took 13 and the one with
-// A^T (15 of 64 lanes live at d = 60) 24.
-template <typename T, int G, int M, bool INIT>
-__global__ __launch_bounds__(kPassThreads) void lsqr_pass_kernel(const T* __restrict__ A, int64_t n, int64_t d,
+// t_i = A[i,:] z - alpha u_i (or b_i when init), partial[g] = sum of t_i^2
+// over the workgroup's rows.  A 16-lane group takes a row: lane l reads
+// elements 64 m + 4 l .. + 3 (one vector load per 64 columns), against z in
+// registers (M blocks of 64 columns; M = 0: any width, z in LDS).  256 rows at
+// a time: the 64 groups of 1024 lanes leave their t_i in LDS, from which 16
+// lanes of the first wave carry the 16 chains of squares (chain s takes the
+// rows s, s + 16, ..) while the others go on.
+// Bound by the latency of one row's chain and the launch when A fits the
+// caches (50000 x 60 FP64, 196 workgroups: 6.4
+// us; 13 with 256 lanes, two rows a group in flight and z read from LDS), by HBM beyond.
+constexpr int kGemvGroup = 16;
+constexpr int kGemvRows = 256;
+template <typename T, int M>
+__global__ __launch_bounds__(kGemvThreads) void lsqr_gemv_kernel(const T* __restrict__ A, int64_t n, int64_t d,
                                                                  int64_t ld, const double* __restrict__ z,
-                                                                 const double* __restrict__ b,
-                                                                 const double* __restrict__ st, double* t,
-                                                                 double* __restrict__ gpart,
-                                                                 double* __restrict__ apart) {
-  constexpr int kSlots = kPassThreads / G;  // rows the workgroup takes at a time
-  constexpr int kCols = 4 * G * M;
-  constexpr int kU = M == 1 ? 4 : 2;        // rows in flight per lane
-  constexpr int kParts = kCols < kPassThreads ? kPassThreads / kCols : 1;
-  __shared__ __align__(16) double red[kSlots * kCols];
-  __shared__ double red2[kParts > 1 ? kPassThreads : 1];
-  __shared__ double sqs[kPassThreads / 64];
-  const double alpha = INIT ? 0.0 : st[0], inv = INIT ? 0.0 : st[6], stop = INIT ? 0.0 : st[4];
-  const int gl = threadIdx.x % G, slot = threadIdx.x / G;
+                                                                 const double* __restrict__ u,
+                                                                 const double* __restrict__ b, int init,
+                                                                 const double* __restrict__ st,
+                                                                 double* __restrict__ t, double* __restrict__ partial) {
+  constexpr int kSlots = kGemvThreads / kGemvGroup;
+  constexpr int kIn = M == 1 ? 4 : M == 2 ? 2 : 1;  // rows in flight per group
+  __shared__ double tb[2][kGemvRows];
+  __shared__ __align__(16) double zs[M == 0 ? 1024 + 4 : 4];
+  if (!init && st[4] != 0.0) return;
+  const double alpha = init ? 0.0 : st[0];
+  const double* src = init ? b : u;
+  const int gl = threadIdx.x % kGemvGroup, slot = threadIdx.x / kGemvGroup;
   const int64_t rows_per_group = (n + gridDim.x - 1) / gridDim.x;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_group, r1 = std::min<int64_t>(n, r0 + rows_per_group);
-  double zc[M][4], acc[M][4];
-  int64_t col[M];  // the lane's columns; lanes past d read column 0 with z = 0
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int64_t c = 4 * G * m + 4 * gl;
-    col[m] = c < d ? c : 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      zc[m][e] = !INIT && c + e < d ? z[c + e] : 0.0;
-      acc[m][e] = 0.0;
-    }
-  }
-  double sq = 0.0;
-  for (int64_t i0 = r0; i0 < r1; i0 += kU * kSlots) {
-    double a[kU][M][4], to[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = std::min<int64_t>(i0 + slot + u * kSlots, r1 - 1);
-#pragma unroll
-      for (int m = 0; m < M; ++m) load4(A + i * ld + col[m], col[m], d, a[u][m]);
-      to[u] = INIT ? b[i] : t[i];
-    }
-    if (stop != 0.0) return;  // (nothing reads this pass's results then)
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t i = i0 + slot + u * kSlots;
-      double ti = to[u];
-      if constexpr (!INIT) {
-        double dot = 0.0;
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dot = fma(a[u][m][e], zc[m][e], dot);
-        ti = row_sum<G>(dot) - alpha * (to[u] * inv);
-      }
-      if (i >= r1) ti = 0.0;
-      if (gl == 0 && i < r1) t[i] = ti;
-      sq = fma(ti, ti, sq);
-#pragma unroll
-      for (int m = 0; m < M; ++m)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[m][e] = fma(ti, a[u][m][e], acc[m][e]);
-    }
-  }
-  // the workgroup's sums
-  sq = wave_sum(gl == 0 ? sq : 0.0);
-  if ((threadIdx.x & 63) == 0) sqs[threadIdx.x >> 6] = sq;
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    double* o = red + slot * kCols + 4 * G * m + 4 * gl;
-    *reinterpret_cast<double2*>(o) = make_double2(acc[m][0], acc[m][1]);
-    *reinterpret_cast<double2*>(o + 2) = make_double2(acc[m][2], acc[m][3]);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < kPassThreads / 64; ++w) s += sqs[w];
-    gpart[blockIdx.x] = s;
-  }
-  if constexpr (kParts > 1) {
-    const int c = threadIdx.x % kCols, p = threadIdx.x / kCols;
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < kSlots / kParts; ++q) s += red[(p + q * kParts) * kCols + c];
-    red2[threadIdx.x] = s;
+  double zc[M == 0 ? 1 : M][4];
+  if constexpr (M == 0) {
+    if (!init)
+      for (int64_t c = threadIdx.x; c < d; c += kGemvThreads) zs[c] = z[c];
     __syncthreads();
-    if (threadIdx.x < kCols && c < d) {
-      s = red2[c];
-#pragma unroll
-      for (int q = 1; q < kParts; ++q) s += red2[q * kCols + c];
-      apart[(int64_t)blockIdx.x * d + c] = s;
-    }
   } else {
-    for (int c = threadIdx.x; c < d; c += kPassThreads) {
-      double s = 0.0;
 #pragma unroll
-      for (int q = 0; q < kSlots; ++q) s += red[q * kCols + c];
-      apart[(int64_t)blockIdx.x * d + c] = s;
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t c = 64 * m + 4 * gl + e;
+        zc[m][e] = !init && c < d ? z[c] : 0.0;
+      }
+  }
+  double sq = 0.0;  // lanes 0 .. 15 of the first wave
+  int buf = 0;
+  for (int64_t i0 = r0; i0 < r1; i0 += kGemvRows, buf ^= 1) {
+    for (int k0 = 0; k0 < kGemvRows / kSlots; k0 += kIn) {
+      double dot[kIn], uv[kIn];
+#pragma unroll
+      for (int q = 0; q < kIn; ++q) uv[q] = src[std::min<int64_t>(i0 + slot + kSlots * (k0 + q), r1 - 1)];
+      if (!init) {
+        if constexpr (M == 0) {
+          const int64_t i = std::min<int64_t>(i0 + slot + kSlots * k0, r1 - 1);
+          double acc = 0.0;
+          for (int64_t c = 4 * gl; c < d; c += 64) {
+            double a[4];
+            load4(A + i * ld + c, c, d, a);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = fma(a[e], c + e < d ? zs[c + e] : 0.0, acc);
+          }
+          dot[0] = acc;
+        } else {
+          double a[kIn][M][4];
+#pragma unroll
+          for (int q = 0; q < kIn; ++q) {
+            const int64_t i = std::min<int64_t>(i0 + slot + kSlots * (k0 + q), r1 - 1);
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+              // lanes past d read column 0 and take zeros
+              const int64_t c = 64 * m + 4 * gl;
+              load4(A + i * ld + (c < d ? c : 0), c, d, a[q][m]);
+              a[q][m][0] = c < d ? a[q][m][0] : 0.0;
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < kIn; ++q) {
+            double acc = 0.0;
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc = fma(a[q][m][e], zc[m][e], acc);
+            dot[q] = acc;
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kIn; ++q) {
+        const int r = slot + kSlots * (k0 + q);
+        const double ti = init ? uv[q] : fma(-alpha, uv[q], ror16_sum(dot[q]));
+        if (gl == 0 && i0 + r < r1) {
+          t[i0 + r] = ti;
+          tb[buf][r] = ti;
+        }
+      }
     }
+    __syncthreads();  // (the other half of tb was read before it)
+    if (threadIdx.x < 16) {
+#pragma unroll
+      for (int k = 0; k < kGemvRows / 16; ++k) {
+        const int r = threadIdx.x + 16 * k;
+        const double ti = tb[buf][r];
+        sq = i0 + r < r1 ? fma(ti, ti, sq) : sq;
+      }
+    }
+  }
+  if (threadIdx.x < 16) {
+    sq = dpp_add<0x4E>(sq);  // chains s and s + 2 of each four, then the two sums
+    sq = dpp_add<0xB1>(sq);
+    double s = __shfl(sq, 0, 16);
+    for (int w = 1; w < 4; ++w) s += __shfl(sq, 4 * w, 16);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
   }
 }
 
-template <typename T, int G, int M>
-void launch_lsqr_pass_gm(bool init, int groups, const T* A, int64_t n, int64_t d, int64_t ld, const double* z,
-                         const double* b, const double* st, double* t, double* gpart, double* apart, hipStream_t s) {
-  const auto kernel = init ? lsqr_pass_kernel<T, G, M, true> : lsqr_pass_kernel<T, G, M, false>;
-  kernel<<<groups, kPassThreads, 0, s>>>(A, n, d, ld, z, b, st, t, gpart, apart);
+// V consecutive elements of a row, widened (V = 4: load4).
+template <typename T, int V>
+__device__ __forceinline__ void load_cols(const T* p, int64_t c, int64_t d, double (&a)[V]) {
+  if constexpr (V == 4) {
+    load4(p, c, d, a);
+  } else if constexpr (V == 1) {
+    a[0] = f64(p[0]);
+  } else if constexpr (sizeof(T) == 8) {
+    const double2 v = *reinterpret_cast<const double2*>(p);
+    a[0] = v.x;
+    a[1] = v.y;
+  } else if constexpr (sizeof(T) == 4) {
+    const float2 v = *reinterpret_cast<const float2*>(p);
+    a[0] = v.x;
+    a[1] = v.y;
+  } else {
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(p);
+    a[0] = (double)__uint_as_float(v << 16);
+    a[1] = (double)__uint_as_float(v & 0xFFFF0000u);
+  }
 }
 
-// The narrowest of the layouts that holds a row.
-template <typename T>
-void launch_lsqr_pass(bool init, int groups, const T* A, int64_t n, int64_t d, int64_t ld, const double* z,
-                      const double* b, const double* st, double* t, double* gpart, double* apart, hipStream_t s) {
-  const auto f = d <= 64    ? launch_lsqr_pass_gm<T, 16, 1>
-                 : d <= 128 ? launch_lsqr_pass_gm<T, 16, 2>
-                 : d <= 256 ? launch_lsqr_pass_gm<T, 16, 4>
-                 : d <= 512 ? launch_lsqr_pass_gm<T, 64, 2>
-                            : launch_lsqr_pass_gm<T, 64, 4>;
-  f(init, groups, A, n, d, ld, z, b, st, t, gpart, apart, s);
+// beta = sqrt(sum of the gemv partials); u = t / beta; partial_g[c] = sum over
+// the workgroup's rows of u_i A[i][c].  Wave w's chain takes every fourth row;
+// lane l takes columns V l .. V l + V - 1 of a slice of 64 V, the narrowest of
+// V = 1, 2, 4 that holds d (V = 4: slice after slice), so all lanes work; the
+// waves' sums are added in LDS in wave order.  u of 256 rows at a time is
+// staged in LDS; kAtvIn rows load together, the next ones while these are
+// added, the first ones before beta is known.
+// Bound like the product with A, and by the sum of the gemv's partials before
+// it (50000 x 60 FP64: 9.3 us; 24 when a lane took four columns at any width,
+// 15 of 64 lanes at d = 60, and waited for beta and for each eight rows).
+constexpr int kAtvThreads = 256;
+template <typename T, int V>
+__global__ __launch_bounds__(kAtvThreads) void lsqr_atv_kernel(const T* __restrict__ A, int64_t n, int64_t d,
+                                                               int64_t ld, const double* __restrict__ t,
+                                                               const double* __restrict__ gpart, int ggroups,
+                                                               double* __restrict__ st, int init,
+                                                               double* __restrict__ u, double* __restrict__ partial) {
+  constexpr int kW = kAtvThreads / 64, kCols = 64 * V, kAtvIn = V == 1 ? 16 : 8;
+  constexpr int kBatch = kW * kAtvIn;  // rows of a batch over the waves
+  __shared__ double red[kW][kCols];
+  __shared__ __align__(16) double gs[1024];
+  __shared__ double ub[kAtvThreads];
+  const int64_t rows_per_group = (n + gridDim.x - 1) / gridDim.x;
+  const int64_t r0 = (int64_t)blockIdx.x * rows_per_group, r1 = std::min<int64_t>(n, r0 + rows_per_group);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double a[2][kAtvIn][V];
+  // the batch of rows from i (this wave: i + wave, + 4, ..), clamped to the
+  // last row; lanes past d read column 0 and are dropped
+  auto load = [&](auto set, int64_t i, int64_t cl) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int q = 0; q < kAtvIn; ++q)
+      load_cols<T, V>(A + std::min<int64_t>(i + wave + kW * q, r1 - 1) * ld + cl, cl, d, a[S][q]);
+  };
+  const std::integral_constant<int, 0> s0;
+  const std::integral_constant<int, 1> s1;
+  const int64_t cl0 = V * lane < d ? V * lane : 0;
+  if (r0 < r1) load(s0, r0, cl0);  // (does not wait for beta)
+  for (int g = threadIdx.x; g < 1024; g += kAtvThreads) gs[g] = g < ggroups ? gpart[g] : 0.0;
+  if (!init && st[4] != 0.0) return;
+  __syncthreads();
+  double s = 0.0;
+  for (int g0 = 0; g0 < ggroups; g0 += 32) {
+    double2 v[16];  // (sums of squares from g0 on, zero past the last: it changes no bit)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = *reinterpret_cast<const double2*>(gs + g0 + 2 * q);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      s += v[q].x;
+      s += v[q].y;
+    }
+  }
+  const double beta = sqrt(s);
+  const double inv = beta > 0.0 ? 1.0 / beta : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st[1] = beta;
+    if (init) {
+      st[5] = beta;
+      st[3] = beta;  // phibar = beta_1
+    }
+  }
+  for (int64_t c0 = 0; c0 < d; c0 += kCols) {
+    const int64_t cl = c0 + V * lane < d ? c0 + V * lane : 0;
+    double acc[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] = 0.0;
+    auto use = [&](auto set, int64_t i0, int k0) {
+      constexpr int S = decltype(set)::value;
+      double ui[kAtvIn];
+#pragma unroll
+      for (int q = 0; q < kAtvIn; ++q) ui[q] = ub[k0 + wave + kW * q];
+#pragma unroll
+      for (int q = 0; q < kAtvIn; ++q)
+        if (i0 + k0 + wave + kW * q < r1) {  // uniform
+#pragma unroll
+          for (int e = 0; e < V; ++e) acc[e] = fma(ui[q], a[S][q][e], acc[e]);
+        }
+    };
+    if (c0 > 0 && r0 < r1) load(s0, r0, cl);
+    for (int64_t i0 = r0; i0 < r1; i0 += kAtvThreads) {
+      __syncthreads();  // the previous rows' u (and the previous slice's sums) have been read
+      const int64_t iu = i0 + threadIdx.x;
+      if (iu < r1) {
+        const double ui = t[iu] * inv;
+        ub[threadIdx.x] = ui;
+        if (c0 == 0) u[iu] = ui;
+      }
+      __syncthreads();
+      for (int k0 = 0; k0 < kAtvThreads; k0 += 2 * kBatch) {
+        if (i0 + k0 + kBatch >= r1) {
+          use(s0, i0, k0);
+          break;
+        }
+        load(s1, i0 + k0 + kBatch, cl);
+        use(s0, i0, k0);
+        if (i0 + k0 + 2 * kBatch >= r1) {
+          use(s1, i0, k0 + kBatch);
+          break;
+        }
+        load(s0, i0 + k0 + 2 * kBatch, cl);
+        use(s1, i0, k0 + kBatch);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) red[wave][V * lane + e] = acc[e];
+    __syncthreads();
+    const int64_t cc = c0 + threadIdx.x;
+    if (threadIdx.x < kCols && cc < d) {
+      double v = red[0][threadIdx.x];
+#pragma unroll
+      for (int w = 1; w < kW; ++w) v += red[w][threadIdx.x];
+      partial[(int64_t)blockIdx.x * d + cc] = v;
+    }
+    __syncthreads();
+  }
 }
 
-// One LSQR step after the pass (init: the first alpha, v, w).  Thread (c, p)
-// of 1024 takes column c and every P-th of the terms of its sums (P = 1024
-// over the power of two that holds d), and the P parts meet in LDS, so the
-// whole workgroup loads; SPAN = 1 or 2 (d <= 64 SPAN) also holds its pieces
-// of N in registers, fetched before the sums that they wait for.  z = N v
-// takes a 16-lane group per row there, a wave per row beyond.
+// One LSQR step after the two passes (init: the first alpha, v, w).  C: the
+// power of two from 64 that holds d.  Every sum runs in eight chains (term j
+// in chain j mod 8, the last j < 8 terms past the whole eights in chain 0)
+// that are added in order; thread (c, p) carries 8 / P of column c's chains,
+// so the whole workgroup loads, and for C <= 128 it holds its pieces of N in
+// registers, fetched before the sums that they wait for.  z = N v takes a
+// 16-lane group per row there, a wave per row beyond.
 //
 // One workgroup: bound by the latency of its chain (partials, N^T, alpha, v,
-// z).  The square roots and divisions are long FP64 sequences, so a single
-// wave runs each: the last wave finds beta and the rotation while the first
-// ones sum the columns, and only the columns' own waves find alpha; run by
-// all sixteen waves they filled the SIMDs.
-// d = 60, 391 partials: 7.9 us (15.7 before, when a column had one thread).
-template <int SPAN>
-__global__ __launch_bounds__(kStepThreads) void lsqr_step_kernel(int64_t d, const double* __restrict__ N,
-                                                                 const double* __restrict__ apart,
-                                                                 const double* __restrict__ gpart, int groups,
-                                                                 double* __restrict__ st, double* __restrict__ v,
-                                                                 double* __restrict__ w, double* __restrict__ y,
-                                                                 double* __restrict__ z, double* __restrict__ hist,
-                                                                 int64_t it, int init) {
-  constexpr int kWaves = kStepThreads / 64;
-  __shared__ double g[1024];
-  __shared__ double part[kStepThreads];
-  __shared__ double red[kWaves];
-  __shared__ double sc[6];  // beta, 1 / beta, phi / rho, sin / rho, cos, sin
+// z).  The square roots and divisions are long FP64 sequences, so the last
+// wave alone takes the rotation and the columns' own waves alpha; run by all
+// sixteen waves they filled the SIMDs.
+// d = 60, 196 partials: 6.0 us (15.7 with one thread a column).
+template <int C>
+__global__ __launch_bounds__(C == 64 ? 512 : 1024) void lsqr_step_kernel(
+    int64_t d, const double* __restrict__ N, const double* __restrict__ partial, int groups, double* __restrict__ st,
+    double* __restrict__ v, double* __restrict__ w, double* __restrict__ y, double* __restrict__ z,
+    double* __restrict__ hist, int64_t it, int init) {
+#pragma clang fp contract(off)  // (a product that ends a chain must not join the sum over the chains)
+  constexpr int kThreads = C == 64 ? 512 : 1024, kWaves = kThreads / 64;
+  constexpr int P = kThreads / C, kU = 8 / P;     // parts, chains of a thread
+  constexpr bool kHold = C <= 128;
+  constexpr int kE = kHold ? C / 8 : 1, kZ = kHold ? C / 16 : 1, kZr = kHold ? C / (kThreads / 16) : 1;
+  __shared__ double g[C];
+  __shared__ double part[8][C];
+  __shared__ double red[C / 64];
+  __shared__ double sc[4];  // phi / rho, sin, cos, rho
   const int di = (int)d;
-  int lc = SPAN == 1 ? 6 : 7;  // log2 of the columns
-  if constexpr (SPAN == 0)
-    while ((1 << lc) < di) ++lc;
-  const int C = 1 << lc, P = kStepThreads >> lc;
-  const int c = threadIdx.x & (C - 1), p = threadIdx.x >> lc;
+  const int c = threadIdx.x & (C - 1), p = threadIdx.x / C;
   const int cl = c < di ? c : 0;  // columns past d load column 0 and are dropped
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool own = p == 0 && c < di;
-  // N's pieces: thread (c, p) the entries N[p + P e][c] of q, the 16-lane
-  // group r the entries N[r + 64 m][l + 16 j] of z
-  constexpr int kE = SPAN == 0 ? 1 : 4 * SPAN * SPAN, kZ = SPAN == 0 ? 1 : 4 * SPAN;
-  double nq[kE], nz[SPAN == 0 ? 1 : SPAN][kZ];
   const int gl = threadIdx.x & 15, gr = threadIdx.x >> 4;
-  // beta^2 = the sum of the gpart, and the sums of the columns' partials:
-  // kU loads in flight, added in a fixed order
-  double bs = 0.0;
-  for (int gg = threadIdx.x; gg < groups; gg += kStepThreads) bs += gpart[gg];
-  constexpr int kU = 16;
-  double sp[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int g0 = p; g0 < groups; g0 += P * kU) {
-    double a[kU];
+  // the partials' chains, sixteen loads in flight
+  const int whole = groups / 8;
+  double sp[kU];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) a[u] = apart[(int64_t)std::min(g0 + P * u, groups - 1) * d + cl];
+  for (int u = 0; u < kU; ++u) sp[u] = 0.0;
+  constexpr int kIn = 16 / kU;
+  for (int k0 = 0; k0 < whole; k0 += kIn) {
+    double a[kIn][kU];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) sp[u & 3] += g0 + P * u < groups ? a[u] : 0.0;
+    for (int q = 0; q < kIn; ++q)
+#pragma unroll
+      for (int u = 0; u < kU; ++u)
+        a[q][u] = partial[(int64_t)(8 * std::min(k0 + q, whole - 1) + p * kU + u) * d + cl];
+#pragma unroll
+    for (int q = 0; q < kIn; ++q)
+      if (k0 + q < whole) {  // uniform
+#pragma unroll
+        for (int u = 0; u < kU; ++u) sp[u] += a[q][u];
+      }
   }
-  const double stop = init ? 0.0 : st[4], rhobar = st[2], phibar = st[3], beta1 = st[5];
+  if (p == 0) {
+    double a[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) a[q] = partial[(int64_t)std::min(8 * whole + q, groups - 1) * d + cl];
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+      if (8 * whole + q < groups) sp[0] += a[q];
+  }
+  const double stop = init ? 0.0 : st[4], beta = st[1], rhobar = st[2], phibar = st[3], beta1 = st[5];
   const double vo = own && !init ? v[c] : 0.0, wo = own && !init ? w[c] : 0.0, yo = own && !init ? y[c] : 0.0;
-  if constexpr (SPAN > 0) {
+  // N's pieces: thread (c, p) the entries N[8 e + p][c] of q, the 16-lane
+  // group r the entries N[r + groups m][l + 16 j] of z
+  double nq[kE], nr[kHold ? 7 : 1], nz[kZr][kZ];
+  const int dw = di / 8;
+  if constexpr (kHold) {
 #pragma unroll
-    for (int e = 0; e < kE; ++e) nq[e] = N[(int64_t)std::min(p + P * e, di - 1) * d + cl];
+    for (int e = 0; e < kE; ++e) nq[e] = N[(int64_t)std::min(8 * e + p, di - 1) * d + cl];
+    if (p == 0)
 #pragma unroll
-    for (int m = 0; m < SPAN; ++m)
+      for (int q = 0; q < 7; ++q) nr[q] = N[(int64_t)std::min(8 * dw + q, di - 1) * d + cl];
+#pragma unroll
+    for (int m = 0; m < kZr; ++m)
 #pragma unroll
       for (int j = 0; j < kZ; ++j) {
-        const int r = gr + 64 * m, cc = gl + 16 * j;
+        const int r = gr + kThreads / 16 * m, cc = gl + 16 * j;
         nz[m][j] = N[(int64_t)(r < di ? r : 0) * d + (cc < di ? cc : 0)];
       }
   }
@@ -473,69 +592,60 @@ __global__ __launch_bounds__(kStepThreads) void lsqr_step_kernel(int64_t d, cons
     if (threadIdx.x == 0 && hist != nullptr) hist[it] = phibar;
     return;
   }
-  part[threadIdx.x] = (sp[0] + sp[1]) + (sp[2] + sp[3]);
-  bs = wave_sum(bs);
-  if (lane == 0) red[wave] = bs;
-  __syncthreads();
-  // g = A^T t (its 1 / beta comes in with q), and beta
-  if (p == 0) {
-    double s = part[c];
 #pragma unroll
-    for (int q = 1; q < P; ++q) s += part[(q << lc) + c];
+  for (int u = 0; u < kU; ++u) part[p * kU + u][c] = sp[u];
+  __syncthreads();
+  if (p == 0) {
+    double s = part[0][c];
+#pragma unroll
+    for (int u = 1; u < 8; ++u) s += part[u][c];
     g[c] = c < di ? s : 0.0;
   }
-  if (wave == kWaves - 1) {
-    double b2 = 0.0;
-#pragma unroll
-    for (int wv = 0; wv < kWaves; ++wv) b2 += red[wv];
-    const double beta = sqrt(b2);
-    if (lane == 0) {
-      sc[0] = beta;
-      sc[1] = beta > 0.0 ? 1.0 / beta : 0.0;
-    }
-  }
   __syncthreads();
-  const double beta = sc[0], inv = sc[1];
-  // N^T g, in P parts
-  double qs = 0.0;
-  if constexpr (SPAN > 0) {
+  // the chains of q = N^T g
 #pragma unroll
-    for (int e = 0; e < kE; ++e) qs = fma(nq[e], g[p + P * e], qs);  // (g is 0 past d)
+  for (int u = 0; u < kU; ++u) sp[u] = 0.0;
+  if constexpr (kHold) {
+#pragma unroll
+    for (int e = 0; e < kE; ++e) sp[0] = e < dw ? fma(nq[e], g[8 * e + p], sp[0]) : sp[0];
+    if (p == 0)
+#pragma unroll
+      for (int q = 0; q < 7; ++q) sp[0] = 8 * dw + q < di ? fma(nr[q], g[std::min(8 * dw + q, C - 1)], sp[0]) : sp[0];
   } else {
-    double sq[8];
+#pragma unroll 4
+    for (int k = 0; k < dw; ++k)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) sq[u] = 0.0;
-    int i = p;
-    for (; i + P * 7 < di; i += P * 8)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) sq[u] = fma(N[(int64_t)(i + P * u) * d + cl], g[i + P * u], sq[u]);
-    for (; i < di; i += P) sq[0] = fma(N[(int64_t)i * d + cl], g[i], sq[0]);
-    qs = ((sq[0] + sq[1]) + (sq[2] + sq[3])) + ((sq[4] + sq[5]) + (sq[6] + sq[7]));
+      for (int u = 0; u < kU; ++u)
+        sp[u] = fma(N[(int64_t)(8 * k + p * kU + u) * d + cl], g[8 * k + p * kU + u], sp[u]);
+    if (p == 0)
+      for (int i = 8 * dw; i < di; ++i) sp[0] = fma(N[(int64_t)i * d + cl], g[i], sp[0]);
   }
-  part[threadIdx.x] = qs;
+#pragma unroll
+  for (int u = 0; u < kU; ++u) part[p * kU + u][c] = sp[u];
   __syncthreads();
-  // q = N^T g / beta - beta v, alpha = ||q||; the last wave: the rotation
+  // q, alpha = ||q||; the last wave: the rotation
   double qc = 0.0, a2 = 0.0;
   if (p == 0) {
-    qc = qs;
+    double s = part[0][c];
 #pragma unroll
-    for (int q = 1; q < P; ++q) qc += part[(q << lc) + c];
-    qc = c < di ? qc * inv - beta * vo : 0.0;
+    for (int u = 1; u < 8; ++u) s += part[u][c];
+    qc = c < di ? (init ? s : fma(-beta, vo, s)) : 0.0;
     a2 = wave_sum(qc * qc);
-    if (SPAN != 1 && lane == 0) red[wave] = a2;
+    if (C > 64 && lane == 0) red[wave] = a2;
   }
   if (wave == kWaves - 1 && !init) {
     const double rho = hypot(rhobar, beta);
     const double cs = rhobar / rho, sn = beta / rho;
-    const double pr = cs * phibar / rho, sr = sn / rho;
+    const double phi = cs * phibar;
+    const double pr = phi / rho;
     if (lane == 0) {
-      sc[2] = pr;
-      sc[3] = sr;
-      sc[4] = cs;
-      sc[5] = sn;
+      sc[0] = pr;
+      sc[1] = sn;
+      sc[2] = cs;
+      sc[3] = rho;
     }
   }
-  if constexpr (SPAN != 1) {
+  if constexpr (C > 64) {
     __syncthreads();
     a2 = 0.0;
     if (p == 0)
@@ -545,20 +655,25 @@ __global__ __launch_bounds__(kStepThreads) void lsqr_step_kernel(int64_t d, cons
   if (p == 0) {
     alpha = sqrt(a2);
     const double ia = alpha > 0.0 ? 1.0 / alpha : 0.0;
-    qc *= ia;                   // the new v
-    g[c] = qc;                  // (still 0 past d)
+    qc *= ia;  // the new v
+    g[c] = qc;  // (v in LDS for z below; 0 past d)
     if (c < di) v[c] = qc;
   }
   __syncthreads();
-  // z = N v for the next pass
-  if constexpr (SPAN > 0) {
+  // z = N v for the next product, summed like a wave per row: each lane its
+  // columns ascending, then partners 32, 16, 8, 4, 2, 1 apart
+  if constexpr (kHold) {
 #pragma unroll
-    for (int m = 0; m < SPAN; ++m) {
-      double zr = 0.0;
+    for (int m = 0; m < kZr; ++m) {
+      double e[4];
 #pragma unroll
-      for (int j = 0; j < kZ; ++j) zr = fma(nz[m][j], g[gl + 16 * j], zr);
-      zr = row16_sum(zr);
-      if (gl == 0 && gr + 64 * m < di) z[gr + 64 * m] = zr;
+      for (int j = 0; j < 4; ++j) {
+        e[j] = nz[m][j] * g[gl + 16 * j];
+        if constexpr (C == 128) e[j] = 64 + gl + 16 * j < di ? fma(nz[m][4 + j], g[64 + gl + 16 * j], e[j]) : e[j];
+      }
+      const double zr = ror16_sum((e[0] + e[2]) + (e[1] + e[3]));
+      const int r = gr + kThreads / 16 * m;
+      if (gl == 0 && r < di) z[r] = zr;
     }
   } else {
     for (int r = wave; r < di; r += kWaves) {
@@ -569,23 +684,25 @@ __global__ __launch_bounds__(kStepThreads) void lsqr_step_kernel(int64_t d, cons
     }
   }
   if (own) {
-    y[c] = init ? 0.0 : fma(sc[2], wo, yo);
-    w[c] = init ? qc : qc - sc[3] * alpha * wo;
+    if (init) {
+      w[c] = qc;
+      y[c] = 0.0;
+    } else {
+      const double theta = sc[1] * alpha;
+      y[c] = fma(sc[0], wo, yo);
+      w[c] = fma(-(theta / sc[3]), wo, qc);
+    }
   }
   if (threadIdx.x == 0) {
     st[0] = alpha;
-    st[1] = beta;
-    st[6] = inv;
     if (init) {
       st[2] = alpha;  // rhobar = alpha_1
-      st[3] = beta;   // phibar = beta_1
-      st[5] = beta;
     } else {
-      st[2] = -sc[4] * alpha;
-      st[3] = sc[5] * phibar;
-      if (hist != nullptr) hist[it] = sc[5] * phibar;
+      st[2] = -sc[2] * alpha;
+      st[3] = sc[1] * phibar;
+      if (hist != nullptr) hist[it] = sc[1] * phibar;
     }
-    if (alpha == 0.0 || (!init && beta == 0.0) || (init ? beta : beta1) == 0.0) st[4] = 1.0;
+    if (alpha == 0.0 || (!init && beta == 0.0) || beta1 == 0.0) st[4] = 1.0;
   }
 }
 
@@ -606,7 +723,8 @@ hipError_t lsqr_typed(const void* Av, int64_t n, int64_t d, int64_t ld, const do
   const T* A = static_cast<const T*>(Av);
   const int groups = lsqr_groups(n);
   double* st = ws;               // 8
-  double* t = st + 8;            // n
+  double* u = st + 8;            // n
+  double* t = u + n;             // n
   double* gpart = t + n;         // groups
   double* apart = gpart + groups;  // groups * d
   double* v = apart + (size_t)groups * d;  // d
@@ -615,14 +733,25 @@ hipError_t lsqr_typed(const void* Av, int64_t n, int64_t d, int64_t ld, const do
   double* z = y + d;
   hipError_t e = launch_fill_zero(st, 8 * sizeof(double), s);
   if (e != hipSuccess) return e;
-  auto pass = [&](bool init) { launch_lsqr_pass<T>(init, groups, A, n, d, ld, z, b, st, t, gpart, apart, s); };
-  const auto step = d <= 64 ? lsqr_step_kernel<1> : d <= 128 ? lsqr_step_kernel<2> : lsqr_step_kernel<0>;
+  const auto gemv = d <= 64    ? lsqr_gemv_kernel<T, 1>
+                    : d <= 128 ? lsqr_gemv_kernel<T, 2>
+                    : d <= 256 ? lsqr_gemv_kernel<T, 4>
+                               : lsqr_gemv_kernel<T, 0>;
+  const auto atv = d <= 64 ? lsqr_atv_kernel<T, 1> : d <= 128 ? lsqr_atv_kernel<T, 2> : lsqr_atv_kernel<T, 4>;
+  const auto step = d <= 64    ? lsqr_step_kernel<64>
+                    : d <= 128 ? lsqr_step_kernel<128>
+                    : d <= 256 ? lsqr_step_kernel<256>
+                    : d <= 512 ? lsqr_step_kernel<512>
+                               : lsqr_step_kernel<1024>;
+  const int step_threads = d <= 64 ? 512 : 1024;
   // beta_1 u_1 = b; alpha_1 v_1 = M^T u_1
-  pass(true);
-  step<<<1, kStepThreads, 0, s>>>(d, N, apart, gpart, groups, st, v, w, y, z, hist, 0, 1);
+  gemv<<<groups, kGemvThreads, 0, s>>>(A, n, d, ld, z, u, b, 1, st, t, gpart);
+  atv<<<groups, kAtvThreads, 0, s>>>(A, n, d, ld, t, gpart, groups, st, 1, u, apart);
+  step<<<1, step_threads, 0, s>>>(d, N, apart, groups, st, v, w, y, z, hist, 0, 1);
   for (int64_t it = 0; it < iters; ++it) {
-    pass(false);
-    step<<<1, kStepThreads, 0, s>>>(d, N, apart, gpart, groups, st, v, w, y, z, hist, it, 0);
+    gemv<<<groups, kGemvThreads, 0, s>>>(A, n, d, ld, z, u, b, 0, st, t, gpart);
+    atv<<<groups, kAtvThreads, 0, s>>>(A, n, d, ld, t, gpart, groups, st, 0, u, apart);
+    step<<<1, step_threads, 0, s>>>(d, N, apart, groups, st, v, w, y, z, hist, it, 0);
   }
   lsqr_finish_kernel<<<(unsigned)((d + 3) / 4), 256, 0, s>>>(d, N, y, x);
   return hipGetLastError();
@@ -636,10 +765,10 @@ hipError_t launch_precondition(int method, int64_t d, const double* R, const int
   if (method == 1) {
     if (d > 128) return hipErrorInvalidValue;
     const int64_t dd = d + (d & 1);
-    const bool narrow = d <= 64;  // a column's elements in its eight lanes: 4 or 8 pairs each
-    const size_t lds = sizeof(double) * (size_t)(dd * svd_stride(narrow ? 4 : 8));  // <= 144 KiB
+    const int elems = d <= 64 ? 4 : 8;  // of a column in a lane of its group
+    const size_t lds = sizeof(double) * (size_t)(dd * svd_stride(elems));  // <= 144 KiB
     const int threads = (int)std::max<int64_t>(64, (dd / 2 * kSvdGroup + 63) / 64 * 64);
-    const auto kernel = narrow ? jacobi_svd_kernel<4> : jacobi_svd_kernel<8>;
+    const auto kernel = d <= 64 ? jacobi_svd_kernel<4> : jacobi_svd_kernel<8>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -667,14 +796,10 @@ hipError_t launch_flag_error(const int32_t* err, int64_t* k_out, hipStream_t s) 
   return hipGetLastError();
 }
 
-// At least 128 rows a workgroup (four per 16-lane group) and at most two
-// workgroups a CU, which hold the loads that HBM's rate asks for.  Fewer
-// workgroups make the pass longer by what the step gains: 50000 x 60 takes
-// 5.8 + 7.9 us at 391 of them, 7.2 + 6.6 at 261.
-int lsqr_groups(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, (n + 127) / 128)); }
+int lsqr_groups(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (n + 255) / 256)); }
 
 size_t lsqr_ws_doubles(int64_t n, int64_t d) {
-  return 8 + (size_t)n + (size_t)lsqr_groups(n) * (1 + (size_t)d) + 4 * (size_t)d;
+  return 8 + 2 * (size_t)n + (size_t)lsqr_groups(n) * (1 + (size_t)d) + 4 * (size_t)d;
 }
 
 hipError_t launch_lsqr(int dtype, const void* A, int64_t n, int64_t d, int64_t ld, const double* N, const double* b,

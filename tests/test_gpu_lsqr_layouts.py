@@ -1,6 +1,7 @@
-"""LSQR's row layouts: a 16-lane group or a wave per row, one to four column
-blocks, and the step's column splits, at the edges of each (d = 1, 64 / 65,
-128 / 129, 256, 512 / 513, 1024), with row counts below one round of a
+"""LSQR's column layouts: one, two, four or any number of 64-column blocks in
+the product with A, one, two or four columns a lane in the one with A^T, and
+the step's splits from 64 to 1024 columns, at the edges of each (d = 1, 64 /
+65, 128 / 129, 256, 512 / 513, 1024), with row counts below one round of a
 workgroup, at its edge and past it, against the FP64 oracle's recurrences."""
 
 import numpy as np
@@ -18,7 +19,7 @@ STEPS = 4
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("n,d", [(1, 1), (129, 1), (31, 3), (1025, 63), (1026, 64), (2051, 65), (1300, 128), (2049, 129),
                                  (3001, 256), (4100, 512), (4203, 513), (8195, 1022), (8200, 1024)])
-def test_lsqr_row_layouts(gpu, dtype, n, d):
+def test_lsqr_column_layouts(gpu, dtype, n, d):
     """A few steps on a well-conditioned Gaussian A with a dense, well-
     conditioned N.  A sum of n terms is off by at most n eps (2e-12 here) and
     a step passes an error on by at most kappa(A N)^2 < 1e2 of it in all four
