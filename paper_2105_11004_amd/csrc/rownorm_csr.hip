@@ -21,6 +21,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lev_internal.h"
 
@@ -229,10 +230,11 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_kernel(const T* __res
 // A wave takes 64 consecutive rows.  Lane l of group g (16 lanes) owns
 // columns 4 (l % 16) .. + 3 of the k <= 64 output columns, and a group walks
 // one row's nonzeros 16 at a time: each lane loads one (column id, value),
-// then for each of the 16 entries the group broadcasts it from its lane (DPP
-// row_newbcast, no LDS), reads the 16 bytes of Z_full's row it needs
-// (ds_read_b128: the group reads the whole 256-byte row, conflict-free) and
-// does four FMAs.  A row of at most one nonzero a_ij needs no k-vector:
+// then for each of the 16 entries the group reads the 16 bytes of Z_full's row
+// it needs (ds_read_b128: the group reads the whole 256-byte row, conflict-
+// free) and does four FMAs; the address and the products take the entry from
+// its lane by themselves (DPP row_newbcast on the add and the FMAs, no move
+// and no LDS).  A row of at most one nonzero a_ij needs no k-vector:
 // theta = a_ij^2 ||Z_full[j,:]||^2, from the squared row norms of Z_full
 // kept in LDS beside it, one row a lane.  The other light rows (2 .. 63
 // nonzeros) go four at a time, one per group.  The four groups move in step, so a wave pays for the longest of
@@ -240,9 +242,8 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_kernel(const T* __res
 // (1, 2, 3-4, 5-8, ..., 33-63; counted with ballots, moved with a forward
 // lane permutation), which puts rows of similar length side by side (with
 // power-law row lengths, a third of the group steps did useful work in row
-// order).  Short chunks step one entry at a time up to four, then four at a
-// time.  Heavy rows are split over the four groups, entry c0 + 4 i + g of
-// a 64-entry chunk going to lane i of group g, so a chunk's last partial
+// order).  Heavy rows are split over the four groups, entry c0 + 4 i + g
+// of a 64-entry piece going to lane i of group g, so a row's last partial
 // stretch costs a quarter of its length, and the groups' partial k-vectors
 // are added at the end.
 // Z_full sits in LDS unpadded, 256 bytes a row: a group's 16-lane read is
@@ -250,15 +251,16 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_kernel(const T* __res
 // conflict cycles per LDS instruction, 64 none).  The squares of a row's k-vector
 // are summed over the group with four DPP steps; the group's last lane
 // stores theta.
+//
+// Bound by vector issue (82 % of the cycles at 2^23 x 512 with 16 nonzeros a
+// row: 1575 of a task's 2850 instructions are the additions and FMAs of the
+// entries, the rest the ordering, loads and sums of rows, 40 % of which have
+// one nonzero).  There: 904 us; 1165 when an entry was moved before it was
+// used, each LDS read waited for the one before it, and the sixteen steps over
+// the light rows were unrolled past the instruction cache.
 constexpr int kGZStride = 64;
 constexpr int kHeavy = 64;
-
-template <int U>
-__device__ __forceinline__ int row_bcast_i(int v) {
-  // every lane reads a valid lane of its row and all rows and banks are on, so
-  // the old value is never used (bound_ctrl set: no copy of it is made)
-  return __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xF, 0xF, true);  // row_newbcast:U
-}
+constexpr uint32_t kSpanMask = 0xFFFFFF, kSpan = 0xFFFF00;  // a light row starts at most this far into its task
 
 __device__ __forceinline__ float group_sum16(float v) {
   // prefix within each 16-lane row; lane 15 of the row ends with the total
@@ -269,28 +271,77 @@ __device__ __forceinline__ float group_sum16(float v) {
   return v;
 }
 
-// y += the group's first `steps` (wave-uniform; rounded up to 4 past 4, at
-// most 16) staged entries (col, val); masked entries carry a zero value.
-__device__ __forceinline__ void group_chunk(const float* __restrict__ Zs, int col, float val, int gl, float (&y)[4],
-                                            int steps = 16) {
-#define LEV_GSTEP(U)                                                                                   \
-  {                                                                                                  \
-    const int cu = row_bcast_i<U>(col);                                                              \
-    const float vu = __int_as_float(row_bcast_i<U>(__float_as_int(val)));                            \
-    const float4 z = *reinterpret_cast<const float4*>(Zs + cu * kGZStride + 4 * gl);                 \
-    y[0] = fmaf(vu, z.x, y[0]);                                                                      \
-    y[1] = fmaf(vu, z.y, y[1]);                                                                      \
-    y[2] = fmaf(vu, z.z, y[2]);                                                                      \
-    y[3] = fmaf(vu, z.w, y[3]);                                                                      \
+// The four LDS reads of entries U0 .. U0 + 3: each lane's 16 bytes of the row
+// of Z_full whose byte offset lane U of the group holds (the add takes it from
+// there; s_nop covers a vector write of off just before).
+template <int U0>
+__device__ __forceinline__ void group_read4(const float* __restrict__ Zs, uint32_t off, uint32_t gl16, float4 (&z)[4]) {
+  uint32_t o[4];
+  asm("s_nop 1\n\t"
+      "v_add_u32_dpp %0, %4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_u32_dpp %1, %4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_u32_dpp %2, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_u32_dpp %3, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+      : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3])
+      : "v"(off), "v"(gl16), "n"(U0), "n"(U0 + 1), "n"(U0 + 2), "n"(U0 + 3));
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    z[u] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Zs) + o[u]);
+}
+
+// y += the entries' products, in order; the values come from their lanes.
+template <int U0>
+__device__ __forceinline__ void group_fma4(float val, const float4 (&z)[4], float (&y)[4]) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f32_dpp %0, %4, %5 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %6 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %7 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %8 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %9 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %10 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %11 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %12 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %13 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %14 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %15 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %16 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %0, %4, %17 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %1, %4, %18 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %2, %4, %19 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f32_dpp %3, %4, %20 row_newbcast:%24 row_mask:0xf bank_mask:0xf"
+      : "+&v"(y[0]), "+&v"(y[1]), "+&v"(y[2]), "+&v"(y[3])
+      : "v"(val), "v"(z[0].x), "v"(z[0].y), "v"(z[0].z), "v"(z[0].w), "v"(z[1].x), "v"(z[1].y), "v"(z[1].z),
+        "v"(z[1].w), "v"(z[2].x), "v"(z[2].y), "v"(z[2].z), "v"(z[2].w), "v"(z[3].x), "v"(z[3].y), "v"(z[3].z),
+        "v"(z[3].w), "n"(U0), "n"(U0 + 1), "n"(U0 + 2), "n"(U0 + 3));
+}
+
+// y += the group's first `steps` (wave-uniform; rounded up to fours, at most
+// 16) staged entries (byte offset of Z_full's row, value); masked entries
+// carry offset 0 and a zero value.  Four reads are in flight while the four
+// before them are added.
+__device__ __forceinline__ void group_chunk(const float* __restrict__ Zs, uint32_t off, float val, uint32_t gl16,
+                                            float (&y)[4], int steps) {
+  float4 a[4], b[4];
+  group_read4<0>(Zs, off, gl16, a);
+  if (steps <= 4) {
+    group_fma4<0>(val, a, y);
+    return;
   }
-  LEV_GSTEP(0)
-  if (steps > 1) LEV_GSTEP(1)
-  if (steps > 2) LEV_GSTEP(2)
-  if (steps > 3) LEV_GSTEP(3)
-  if (steps > 4) { LEV_GSTEP(4) LEV_GSTEP(5) LEV_GSTEP(6) LEV_GSTEP(7) }
-  if (steps > 8) { LEV_GSTEP(8) LEV_GSTEP(9) LEV_GSTEP(10) LEV_GSTEP(11) }
-  if (steps > 12) { LEV_GSTEP(12) LEV_GSTEP(13) LEV_GSTEP(14) LEV_GSTEP(15) }
-#undef LEV_GSTEP
+  group_read4<4>(Zs, off, gl16, b);
+  group_fma4<0>(val, a, y);
+  if (steps <= 8) {
+    group_fma4<4>(val, b, y);
+    return;
+  }
+  group_read4<8>(Zs, off, gl16, a);
+  group_fma4<4>(val, b, y);
+  if (steps <= 12) {
+    group_fma4<8>(val, a, y);
+    return;
+  }
+  group_read4<12>(Zs, off, gl16, b);
+  group_fma4<8>(val, a, y);
+  group_fma4<12>(val, b, y);
 }
 
 template <typename T>
@@ -303,64 +354,95 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_grp_kernel(const T* _
   extern __shared__ __align__(16) float Zs[];  // d rows of kGZStride floats, then d squared row norms
   if (col_tile_dead(ct)) return;
   float* zn = Zs + d * kGZStride;
-  for (int64_t e = threadIdx.x; e < d * 64; e += kCsrThreads) Zs[(e / 64) * kGZStride + (e % 64)] = Zg[e];
-  for (int64_t c = threadIdx.x; c < d; c += kCsrThreads) {
-    float a = 0.f;
-    for (int q = 0; q < 64; ++q) a = fmaf(Zg[c * 64 + q], Zg[c * 64 + q], a);
-    zn[c] = a;
+  {
+    const float4* Z4 = reinterpret_cast<const float4*>(Zg);
+#pragma unroll 8
+    for (int e = threadIdx.x; e < (int)d * 16; e += kCsrThreads) reinterpret_cast<float4*>(Zs)[e] = Z4[e];
+    if (threadIdx.x < d) {
+      float4 z[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) z[q] = Z4[threadIdx.x * 16 + q];
+      float a = 0.f;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) a = fmaf(z[q].w, z[q].w, fmaf(z[q].z, z[q].z, fmaf(z[q].y, z[q].y, fmaf(z[q].x, z[q].x, a))));
+      zn[threadIdx.x] = a;
+    }
   }
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, gl = lane & 15;
+  const uint32_t gl16 = 16 * gl;
   const int64_t ntask = (n + 63) / 64;
   const int64_t tstep = (int64_t)gridDim.x * kCsrWaves;
   int64_t task = (int64_t)blockIdx.x * kCsrWaves + wave;
   // the next task's row starts load while the current task runs
   auto row_start = [&](int64_t tk) -> int64_t {
-    if (tk >= ntask) return 0;
-    const int64_t r = tk * 64 + lane;
-    return r <= n ? min(max(row_ptr[r], (int64_t)0), nnz) : nnz;
+    const int64_t r = std::min<int64_t>(tk, ntask - 1) * 64 + lane;
+    return min(max(row_ptr[std::min<int64_t>(r, n)], (int64_t)0), nnz);
   };
   int64_t rp_next = row_start(task);
   for (; task < ntask; task += tstep) {
     const int64_t r0 = task * 64;
+    float* th = theta + r0;
+    auto store = [&](uint32_t r, float sq) { th[r] = ct.acc ? th[r] + sq : sq; };
     const int nr = (int)min((int64_t)64, n - r0);
     // lane j: start of row r0 + j, made non-decreasing
     int64_t rp = rp_next;
     rp_next = row_start(task + tstep);
+    // (the shuffles run on every lane: a lane masked off by a branch does not
+    // supply its value to the others)
+    const int64_t before = __shfl_up(rp, 1, 64);
+    if (__ballot(lane > 0 && before > rp) != 0) {
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int64_t up = __shfl_up(rp, o, 64);
-      if (lane >= o) rp = max(rp, up);
+      for (int o = 1; o < 64; o <<= 1) {
+        const int64_t up = __shfl_up(rp, o, 64);
+        if (lane >= o) rp = max(rp, up);
+      }
     }
     int64_t last = min(max(row_ptr[r0 + nr], (int64_t)0), nnz);
     last = max(last, __shfl(rp, 63, 64));
     if (lane >= nr) rp = last;  // rows past the task's end are empty
-    // (the shuffle runs on every lane: a lane masked off by a branch does not
-    // supply its value to the others)
     const int64_t down = __shfl_down(rp, 1, 64);
     const int64_t rnext = lane < 63 ? down : last;
     const int len = lane < nr ? (int)(rnext - rp) : 0;
-    const uint64_t heavy = __ballot(lane < nr && len >= kHeavy);
-    // rows of at most one nonzero, one a lane (an empty row's theta is 0)
-    if (lane < nr && len <= 1) {
-      float sq = 0.f;
-      if (len == 1) {
-        const int cc = col_idx[rp];
-        const float vv = to_f32<T>(vals[rp]);
-        if ((uint32_t)cc < (uint32_t)d) sq = vv * vv * zn[cc];
-      }
-      const int64_t r = r0 + lane;
-      theta[r] = ct.acc ? theta[r] + sq : sq;
-    }
-    // the other light rows by length class; sorted position q holds row
-    // srow, its start rps and length lens; the rows just done (class 0),
-    // then the heavy rows and lanes past the task's end sort outside
-    // positions n01 .. nlight - 1
     const bool light = lane < nr && len < kHeavy;
+    uint64_t heavy = __ballot(lane < nr && len >= kHeavy);
+
+    // The heavy rows' pieces, 64 entries each, one after the other: entry
+    // c0 + 4 i + g to lane i of group g.  A piece loads while the one before
+    // it is added (the first before the light rows); every load is
+    // unconditional, a lane past the row's end takes the piece's first entry.
+    int hj = 0, hc0 = 0, hlen = 0;  // row, first entry and length of the loaded piece (uniform)
+    int32_t hcol = 0;
+    T hval{};
+    auto heavy_load = [&](int j, int c0) {
+      hj = j;
+      hc0 = c0;
+      hlen = __builtin_amdgcn_readlane(len, j);
+      const int64_t s0 = ((int64_t)__builtin_amdgcn_readlane((int)(rp >> 32), j) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)rp, j);
+      const uint32_t e = 4 * gl + g;
+      const uint32_t at = (int)e < hlen - c0 ? e : 0;
+      hcol = (col_idx + s0 + c0)[at];
+      hval = (vals + s0 + c0)[at];
+    };
+    if (heavy != 0) heavy_load(__builtin_ctzll(heavy), 0);
+
+    // rows of at most one nonzero, one a lane (an empty row's theta is 0)
+    int32_t c1 = 0;
+    T v1{};
+    if (nnz > 0) {
+      const int64_t at = min(rp, nnz - 1);
+      c1 = col_idx[at];
+      v1 = vals[at];
+    }
+    // the other light rows by length class; sorted position q holds a row's
+    // start (from the task's first), its length and its number; the rows of
+    // at most one nonzero (class 0), then the heavy rows and lanes past the
+    // task's end sort outside positions n01 .. nlight - 1
     const int cls = light ? (len <= 1 ? 0 : 32 - __builtin_clz((unsigned)(len - 1))) : 7;
-    int pos = 0, base = 0, nlight = 0, n01 = 0;
+    int pos = 0, base = 0, nlight = 0, n01 = 0, n16 = 0;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const uint64_t m = __ballot(cls == c);
@@ -368,109 +450,128 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_grp_kernel(const T* _
       if (cls == c) pos = base + below;
       base += __popcll(m);
       if (c == 0) n01 = base;
+      if (c == 4) n16 = base;
       if (c == 6) nlight = base;
     }
-    const int srow = __builtin_amdgcn_ds_permute(4 * pos, lane);
-    const int64_t rps = ((int64_t)__builtin_amdgcn_ds_permute(4 * pos, (int)(rp >> 32)) << 32) |
-                        (uint32_t)__builtin_amdgcn_ds_permute(4 * pos, (int)rp);
-    const int lens = __builtin_amdgcn_ds_permute(4 * pos, light ? len : 0);
+    const int64_t first = ((int64_t)__builtin_amdgcn_readfirstlane((int)(rp >> 32)) << 32) |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)rp);
+    // (64 rows of at most d entries span far less; a malformed row_ptr stays in bounds)
+    const int rel = (int)min(rp - first, (int64_t)kSpan);
+    const int rel_s = __builtin_amdgcn_ds_permute(4 * pos, rel);
+    const int row_s = __builtin_amdgcn_ds_permute(4 * pos, (light ? len : 0) | (lane << 8));
+    // the longest of positions q .. q + 3 (past the wave it wraps to rows of
+    // class 0, no longer than these)
+    int longest = row_s & 0xFF;
+    longest = max(longest, __shfl(longest, (lane + 1) & 63, 64));
+    longest = max(longest, __shfl(longest, (lane + 2) & 63, 64));
+    if (light && len <= 1) {
+      float sq = 0.f;
+      if (len == 1 && (uint32_t)c1 < (uint32_t)d) {
+        const float vv = to_f32<T>(v1);
+        sq = vv * vv * zn[c1];
+      }
+      store(lane, sq);
+    }
 
     // light rows of 2 .. 63 nonzeros: group g takes sorted positions
-    // n01 + 4 q + g; the first 32 nonzeros of the rows two steps ahead load
-    // while a step runs (a ring of three); a position at or past nlight
-    // (possibly past the wave) stands for an empty row
-    int pc[3][2];
-    float pv[3][2];
-#define LEV_LOADQ(Q, SLOT)                                                                          \
-    {                                                                                               \
-      const int jj = n01 + 4 * (Q) + g;                                                             \
-      const int64_t ss = __shfl(rps, jj & 63, 64);                                                  \
-      const int lr = __shfl(lens, jj & 63, 64); /* on every lane, then masked */                    \
-      const int ll = jj < nlight ? lr : 0;                                                          \
-      _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                               \
-        const int t = 16 * h + gl;                                                                  \
-        const bool ok = t < ll;                                                                     \
-        const int cc = ok ? col_idx[ss + t] : 0;                                                    \
-        const float vv = ok ? to_f32<T>(vals[ss + t]) : 0.f;                                        \
-        const bool cin = (uint32_t)cc < (uint32_t)d;                                                \
-        pc[SLOT][h] = cin ? cc : 0;                                                                 \
-        pv[SLOT][h] = cin ? vv : 0.f;                                                               \
-      }                                                                                             \
-    }
-    LEV_LOADQ(0, 0)
-    LEV_LOADQ(1, 1)
+    // n01 + 4 q + g; the first 16 nonzeros (32 once rows are longer) of the
+    // rows two steps ahead load while a step runs; a position at or past
+    // nlight stands for an empty row (its lanes load the task's first entry)
+    const int32_t* cb = col_idx + first;
+    const T* vb = vals + first;
+    struct Quad {
+      int32_t c[2];
+      T v[2];
+      uint32_t rel;
+      int row;  // length (0: no row), number << 8
+    };
+    auto quad_load = [&](Quad& x, int q, auto pieces) {
+      const int jj = n01 + 4 * q + g;
+      const int rj = __shfl(rel_s, jj & 63, 64), wj = __shfl(row_s, jj & 63, 64);  // on every lane, then masked
+      x.rel = jj < nlight ? (uint32_t)rj & kSpanMask : 0u;
+      x.row = jj < nlight ? wj : 0;
+      const int ll = x.row & 0xFF;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      if (n01 + 4 * q >= nlight) break;  // uniform: the rest are heavy or past the end
-      if (q + 2 < 16) LEV_LOADQ(q + 2, (q + 2) % 3)
-      const int slot = q % 3;
-      const int j = n01 + 4 * q + g;
-      const bool mine = j < nlight;
-      const int64_t s0 = __shfl(rps, j & 63, 64);
-      const int ljr = __shfl(lens, j & 63, 64);  // on every lane, then masked
-      const int lj = mine ? ljr : 0;
-      // wave-uniform chunk count: the longest of the four groups' rows
-      int mx = lj;
-      mx = max(mx, __shfl_xor(mx, 16, 64));
-      mx = max(mx, __shfl_xor(mx, 32, 64));
+      for (int h = 0; h < decltype(pieces)::value; ++h) {
+        const int t = 16 * h + gl;
+        const uint32_t at = x.rel + (t < ll ? t : 0);
+        x.c[h] = cb[at];
+        x.v[h] = vb[at];
+      }
+      asm volatile("" ::: "memory");  // keeps the loads here
+    };
+    auto staged = [&](int32_t c, T v, bool ok, uint32_t& off, float& val) {
+      const bool in = ok && (uint32_t)c < (uint32_t)d;
+      off = in ? (uint32_t)c * (kGZStride * 4) : 0u;
+      val = in ? to_f32<T>(v) : 0.f;
+    };
+    auto quad_run = [&](const Quad& x, int q, auto pieces) {
+      const int mx = __builtin_amdgcn_readlane(longest, n01 + 4 * q);  // of the four groups' rows
+      const int ll = x.row & 0xFF;
       float y[4] = {0.f, 0.f, 0.f, 0.f};
-      if (mx > 0) group_chunk(Zs, pc[slot][0], pv[slot][0], gl, y, mx);
-      if (mx > 16) group_chunk(Zs, pc[slot][1], pv[slot][1], gl, y, mx - 16);
-      for (int c0 = 32; c0 < mx; c0 += 16) {
-        const int t = c0 + gl;
-        const bool ok = t < lj;
-        const int col = ok ? col_idx[s0 + t] : 0;
-        const float v = ok ? to_f32<T>(vals[s0 + t]) : 0.f;
-        const bool cin = (uint32_t)col < (uint32_t)d;
-        group_chunk(Zs, cin ? col : 0, cin ? v : 0.f, gl, y, mx - c0);
+      uint32_t off;
+      float val;
+      staged(x.c[0], x.v[0], gl < ll, off, val);
+      group_chunk(Zs, off, val, gl16, y, mx);
+      if constexpr (decltype(pieces)::value == 2) {
+        staged(x.c[1], x.v[1], 16 + gl < ll, off, val);
+        group_chunk(Zs, off, val, gl16, y, mx - 16);
+        for (int c0 = 32; c0 < mx; c0 += 16) {
+          const int t = c0 + gl;
+          const uint32_t at = x.rel + (t < ll ? t : 0);
+          staged(cb[at], vb[at], t < ll, off, val);
+          group_chunk(Zs, off, val, gl16, y, mx - c0);
+        }
       }
       const float sq = group_sum16(y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
-      const int sj = __shfl(srow, j & 63, 64);
-      if (mine && gl == 15) {
-        const int64_t r = r0 + sj;
-        theta[r] = ct.acc ? theta[r] + sq : sq;
+      if (ll > 0 && gl == 15) store((uint32_t)x.row >> 8, sq);
+    };
+    auto quads = [&](int q0, int q1, auto pieces) {
+      if (q0 >= q1) return;
+      Quad x0, x1, x2;
+      quad_load(x0, q0, pieces);
+      quad_load(x1, q0 + 1, pieces);
+      for (int q = q0;; q += 3) {
+        quad_load(x2, q + 2, pieces);
+        quad_run(x0, q, pieces);
+        if (q + 1 >= q1) break;
+        quad_load(x0, q + 3, pieces);
+        quad_run(x1, q + 1, pieces);
+        if (q + 2 >= q1) break;
+        quad_load(x1, q + 4, pieces);
+        quad_run(x2, q + 2, pieces);
+        if (q + 3 >= q1) break;
       }
-    }
-#undef LEV_LOADQ
-    // heavy rows: the four groups split each row's nonzeros (entry c0 + 4 i
-    // + g to lane i of group g); the next chunk of 64 loads while the
-    // current one runs
-    uint64_t hm = heavy;
-    while (hm) {
-      const int j = __builtin_ctzll(hm);
-      hm &= hm - 1;
-      const int64_t s0 = __shfl(rp, j, 64);
-      const int lj = __shfl(len, j, 64);
-      auto load = [&](int c0, int& col, float& v) {
-        const int t = c0 + 4 * gl + g;
-        const bool ok = t < lj;
-        const int cc = ok ? col_idx[s0 + t] : 0;
-        const float vv = ok ? to_f32<T>(vals[s0 + t]) : 0.f;
-        const bool cin = (uint32_t)cc < (uint32_t)d;
-        col = cin ? cc : 0;
-        v = cin ? vv : 0.f;
-      };
-      int col;
-      float v;
-      load(0, col, v);
-      float y[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int c0 = 0; c0 < lj; c0 += 64) {
-        int ncol = 0;
-        float nv = 0.f;
-        if (c0 + 64 < lj) load(c0 + 64, ncol, nv);
-        group_chunk(Zs, col, v, gl, y, min(16, (lj - c0 + 3) / 4));
-        col = ncol;
-        v = nv;
-      }
+    };
+    // classes 1 .. 4 are at most 16 long: whole steps of them, then the rest
+    const int nq = (nlight - n01 + 3) / 4, nshort = n16 == nlight ? nq : (n16 - n01) / 4;
+    quads(0, nshort, std::integral_constant<int, 1>());
+    quads(nshort, nq, std::integral_constant<int, 2>());
+
+    // heavy rows: the groups' partial k-vectors are added at the end
+    float y[4] = {0.f, 0.f, 0.f, 0.f};
+    while (heavy != 0) {
+      uint32_t off;
+      float val;
+      const int j = hj, c0 = hc0, lj = hlen;
+      staged(hcol, hval, 4 * gl + g < lj - c0, off, val);
+      const bool done = c0 + 64 >= lj;
+      if (done) heavy &= heavy - 1;
+      // the next piece: of this row or of the next (after the last one, the
+      // first again, not used)
+      heavy_load(done && heavy != 0 ? __builtin_ctzll(heavy) : j, done ? 0 : c0 + 64);
+      asm volatile("" ::: "memory");
+      group_chunk(Zs, off, val, gl16, y, min(16, (lj - c0 + 3) / 4));
+      if (done) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        y[q] += __shfl_xor(y[q], 16, 64);
-        y[q] += __shfl_xor(y[q], 32, 64);
-      }
-      const float sq = group_sum16(y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
-      if (lane == 15) {
-        const int64_t r = r0 + j;
-        theta[r] = ct.acc ? theta[r] + sq : sq;
+        for (int q = 0; q < 4; ++q) {
+          y[q] += __shfl_xor(y[q], 16, 64);
+          y[q] += __shfl_xor(y[q], 32, 64);
+        }
+        const float sq = group_sum16(y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3]);
+        if (lane == 15) store(j, sq);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[q] = 0.f;
       }
     }
   }
