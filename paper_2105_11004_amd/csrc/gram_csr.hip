@@ -9,11 +9,11 @@
 // banks) and one chunk of rows.  A wave takes one row at a time: column ids
 // are sorted within a row, so the entries in block I and in block J are two
 // contiguous runs, found by counting ids below the block bounds (a wave
-// walks 64 rows at a time with their extents in one load, and a row of at
-// most 64 entries is read once, the next row's read in flight, and its
-// pairs of run entries go one per lane, 64 per atomic instruction); a longer
-// row's lanes hold its runs (up to 128 entries each, two per lane) and, for
-// each entry p
+// walks 64 rows at a time with their extents in one load; a row of at
+// most 64 entries is read once, eight rows' reads in flight while the eight
+// before them are added, and its pairs of run entries go one per lane, 64 per
+// atomic instruction); a longer row's lanes hold its runs (up to 128 entries
+// each, two per lane) and, for each entry p
 // of run I in turn (its id and value read from the holding lane), add
 // a_ip a_iq for the entries q of run J, one per lane, by LDS atomic adds.
 // On a diagonal tile only q >= p is added (the upper triangle, mirrored when
@@ -21,11 +21,18 @@
 // into B and mirrored below the diagonal.  FP32 and BF16 values give exact
 // FP64 products; the order of the atomic adds inside a workgroup is not
 // fixed, so B's last bits can vary between runs.
+//
+// Bound by issue: each tile's workgroups walk every row's ids (300007 x 300
+// at 16 nonzeros a row, six tiles: 593 us; 875 when a row's loads stood under
+// a bound with their conversion, so that each row waited for its own, the
+// pairs were dealt out by an integer division, and 516 workgroups made a third
+// round of four on 256 CUs).
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lev_internal.h"
 
@@ -37,6 +44,7 @@ constexpr int kGS = kGT + 1;         // LDS row stride of the tile, in doubles
 constexpr int kGThreads = 1024;      // 16 waves
 constexpr int kGWaves = kGThreads / 64;
 constexpr int kTargetGroups = 512;   // workgroups per launch (one per CU resident: 129 KB of LDS)
+constexpr int kGU = 8;               // rows whose entries load together
 constexpr size_t kTileBytes = sizeof(double) * kGT * kGS;
 
 __device__ __forceinline__ double val_f64(double x) { return x; }
@@ -49,7 +57,7 @@ int64_t tile_pairs(int64_t d) {
   return nb * (nb + 1) / 2;
 }
 int64_t row_chunks(int64_t n, int64_t d) {
-  const int64_t want = (kTargetGroups + tile_pairs(d) - 1) / tile_pairs(d);
+  const int64_t want = kTargetGroups / tile_pairs(d);  // rounded down: one workgroup more would be a round of its own
   return std::max<int64_t>(1, std::min<int64_t>(want, (n + 255) / 256));
 }
 
@@ -92,60 +100,49 @@ __global__ __launch_bounds__(kGThreads) void gram_csr_kernel(const T* __restrict
   const int wave = threadIdx.x >> 6;
   const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk;
   const int64_t r1 = std::min<int64_t>(n, r0 + rows_per_chunk);
-  // The pairs of one row with its entries in registers: entry t (t < lI of
-  // run I, t < lJ of run J) held by lane t % 64, slot t / 64.
-  auto add_pairs = [&](const int32_t (&cI)[2], const double (&vI)[2], const int32_t (&cJ)[2],
-                       const double (&vJ)[2], int lI) {
-    for (int p = 0; p < lI; ++p) {
-      const int h = p >> 6, l = p & 63;
-      const int32_t cp = __builtin_amdgcn_readlane(h ? cI[1] : cI[0], l);
-      const double vp = readlane_f64(h ? vI[1] : vI[0], l);
-      if ((uint32_t)cp >= (uint32_t)kGT) continue;
-      double* row = tile + cp * kGS;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        // diagonal tile: the upper triangle (q >= p, i.e. c_q >= c_p) only
-        if (cJ[q] >= 0 && (!diag || cJ[q] >= cp)) atomicAdd(row + cJ[q], vp * vJ[q]);
-      }
-    }
-  };
   // A wave takes 64 consecutive rows at a time: their extents in one load
   // (lane j: row i0 + j), then row by row.  A row of at most 64 entries is
-  // loaded once (ids and values, one per lane, the next row's load in
-  // flight while this row's pairs are added) and its pairs of run entries
-  // are dealt out one per lane; longer rows count and load their runs from
-  // memory in 64-entry pieces.
+  // loaded once (ids and values, one per lane) and its pairs of run entries
+  // are dealt out one per lane; kGU rows load together, the next kGU while
+  // these are added, every load unconditional.  Longer rows follow: they
+  // count and load their runs from memory in 64-entry pieces.
   for (int64_t i0 = r0 + 64 * (int64_t)wave; i0 < r1; i0 += 64 * (int64_t)kGWaves) {
     const int nr = (int)std::min<int64_t>(64, r1 - i0);
     // row extents clamped to [0, nnz] and made non-decreasing (a malformed
     // row_ptr gives a wrong B, no stray access)
-    int64_t rs = lane < nr ? std::min<int64_t>(std::max<int64_t>(row_ptr[i0 + lane], 0), nnz) : nnz;
-    int64_t re = lane < nr ? std::min<int64_t>(std::max<int64_t>(row_ptr[i0 + lane + 1], 0), nnz) : nnz;
-    re = std::max(re, rs);
-    auto load_short = [&](int j, int32_t& c, double& v) {
-      // entry `lane` of row j when the row has at most 64 entries
-      const int64_t s = ((int64_t)__builtin_amdgcn_readlane((int)(rs >> 32), j) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)rs, j);
-      const int64_t e = ((int64_t)__builtin_amdgcn_readlane((int)(re >> 32), j) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)re, j);
-      const bool ok = e - s <= 64 && s + lane < e;
-      c = ok ? col_idx[s + lane] : INT32_MAX;
-      v = ok ? val_f64(vals[s + lane]) : 0.0;
+    const int64_t ir = i0 + std::min(lane, nr - 1);
+    int64_t rs = std::min<int64_t>(std::max<int64_t>(row_ptr[ir], 0), nnz);
+    const int64_t re = std::max(std::min<int64_t>(std::max<int64_t>(row_ptr[ir + 1], 0), nnz), rs);
+    const int len = lane < nr ? (int)std::min<int64_t>(re - rs, INT32_MAX) : 0;
+    if (len == 0) rs = 0;  // (an empty row's lanes load entry 0)
+    uint64_t longer = __ballot(len > 64);
+    auto start = [&](int j) -> int64_t {
+      return ((int64_t)__builtin_amdgcn_readlane((int)(rs >> 32), j) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane((int)rs, j);
     };
-    int32_t nc;
-    double nv;
-    load_short(0, nc, nv);
-    for (int j = 0; j < nr; ++j) {
-      const int32_t c = nc;
-      const double v = nv;
-      if (j + 1 < nr) load_short(j + 1, nc, nv);
-      const int64_t s = ((int64_t)__builtin_amdgcn_readlane((int)(rs >> 32), j) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)rs, j);
-      const int64_t e = ((int64_t)__builtin_amdgcn_readlane((int)(re >> 32), j) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)re, j);
-      const int64_t len = e - s;
-      if (len == 0) continue;
-      if (len <= 64) {
+    int32_t cs[2][kGU];
+    T vs[2][kGU];
+    int ls[2][kGU];  // uniform
+    auto load = [&](auto set, int g) {
+      constexpr int S = decltype(set)::value;
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        const int j = (g + u) & 63;
+        const int64_t st = start(j);
+        ls[S][u] = __builtin_amdgcn_readlane(len, j);
+        const uint32_t t = lane < ls[S][u] ? lane : 0;
+        cs[S][u] = (col_idx + st)[t];
+        vs[S][u] = (vals + st)[t];
+      }
+      asm volatile("" ::: "memory");  // keeps the loads here
+    };
+    auto add = [&](auto set) {
+      constexpr int S = decltype(set)::value;
+#pragma unroll
+      for (int u = 0; u < kGU; ++u) {
+        if (ls[S][u] == 0 || ls[S][u] > 64) continue;  // uniform
+        const int32_t c = lane < ls[S][u] ? cs[S][u] : INT32_MAX;
+        const double v = val_f64(vs[S][u]);
         // positions of the runs [I0, Iend) and [J0, Jend) among the sorted ids
         const int loI = __popcll(__ballot(c < I0)), hiI = __popcll(__ballot(c < Iend));
         const int loJ = __popcll(__ballot(c < J0)), hiJ = __popcll(__ballot(c < Jend));
@@ -153,11 +150,13 @@ __global__ __launch_bounds__(kGThreads) void gram_csr_kernel(const T* __restrict
         if (lI <= 0 || lJ <= 0) continue;
         // one lane per pair (p, q) of the two runs, 64 pairs per step: the
         // entries come from their lanes by shuffles that every lane takes
-        // part in
+        // part in.  p = k / lJ by a reciprocal: (k + 1/2) / lJ is at least
+        // 1 / 128 from a whole number, far beyond its error below 2^12
         const int np = lI * lJ;
+        const float rl = 1.0f / (float)lJ;
         for (int k0 = 0; k0 < np; k0 += 64) {
           const int k = k0 + lane;
-          const int pp = k / lJ, qq = k - pp * lJ;
+          const int pp = (int)(((float)k + 0.5f) * rl), qq = k - pp * lJ;
           const bool ok = k < np;
           const int srcp = ok ? loI + pp : 0, srcq = ok ? loJ + qq : 0;
           const int32_t cp = __shfl(c, srcp, 64) - I0, cq = __shfl(c, srcq, 64) - J0;
@@ -167,32 +166,80 @@ __global__ __launch_bounds__(kGThreads) void gram_csr_kernel(const T* __restrict
           if (ok && (uint32_t)cp < (uint32_t)kGT && (uint32_t)cq < (uint32_t)kGT && (!diag || cq >= cp))
             atomicAdd(tile + cp * kGS + cq, vp * vq);
         }
-        continue;
       }
-      int32_t cI[2], cJ[2];
-      double vI[2], vJ[2];
+    };
+    const std::integral_constant<int, 0> s0;
+    const std::integral_constant<int, 1> s1;
+    load(s0, 0);
+    for (int g = 0;; g += 2 * kGU) {
+      if (g + kGU >= nr) {
+        add(s0);
+        break;
+      }
+      load(s1, g + kGU);
+      add(s0);
+      if (g + 2 * kGU >= nr) {
+        add(s1);
+        break;
+      }
+      load(s0, g + 2 * kGU);
+      add(s1);
+    }
+    for (; longer != 0; longer &= longer - 1) {
+      const int j = __builtin_ctzll(longer);
+      const int64_t st = start(j);
+      const int ln = __builtin_amdgcn_readlane(len, j);
+      const int32_t* rc = col_idx + st;
+      const T* rv = vals + st;
       int loI = 0, hiI = 0, loJ = 0, hiJ = 0;
-      for (int64_t c0 = s; c0 < e; c0 += 64) {
-        const int64_t p = c0 + lane;
-        const int32_t cc = p < e ? col_idx[p] : INT32_MAX;
-        loI += __popcll(__ballot(cc < I0));
-        hiI += __popcll(__ballot(cc < Iend));
-        loJ += __popcll(__ballot(cc < J0));
-        hiJ += __popcll(__ballot(cc < Jend));
+      for (int c0 = 0; c0 < ln; c0 += 4 * 64) {
+        int32_t c4[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c4[q] = rc[std::min(c0 + 64 * q + lane, ln - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int32_t cc = c0 + 64 * q + lane < ln ? c4[q] : INT32_MAX;
+          loI += __popcll(__ballot(cc < I0));
+          hiI += __popcll(__ballot(cc < Iend));
+          loJ += __popcll(__ballot(cc < J0));
+          hiJ += __popcll(__ballot(cc < Jend));
+        }
       }
       const int lI = std::min(hiI - loI, kGT), lJ = std::min(hiJ - loJ, kGT);
       if (lI <= 0 || lJ <= 0) continue;
+      // entry t of run I and of run J held by lane t % 64, slot t / 64
+      int32_t cI[2], cJ[2];
+      T vI[2], vJ[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int t = lane + 64 * h;
-        const int64_t pi = s + loI + t, pj = s + loJ + t;
-        cI[h] = t < lI ? col_idx[pi] - I0 : 0;
-        vI[h] = t < lI ? val_f64(vals[pi]) : 0.0;
-        cJ[h] = t < lJ ? col_idx[pj] - J0 : -1;
-        vJ[h] = t < lJ ? val_f64(vals[pj]) : 0.0;
-        if ((uint32_t)cJ[h] >= (uint32_t)kGT) cJ[h] = -1;
+        const int pi = loI + std::min(t, lI - 1), pj = loJ + std::min(t, lJ - 1);
+        cI[h] = rc[pi];
+        vI[h] = rv[pi];
+        cJ[h] = rc[pj];
+        vJ[h] = rv[pj];
       }
-      add_pairs(cI, vI, cJ, vJ, lI);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        cI[h] -= I0;
+        cJ[h] = lane + 64 * h < lJ && (uint32_t)(cJ[h] - J0) < (uint32_t)kGT ? cJ[h] - J0 : -1;
+      }
+      const double wJ[2] = {val_f64(vJ[0]), val_f64(vJ[1])};
+      // each entry p of run I against run J, one entry of it a lane
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double wI = val_f64(vI[h]);
+#pragma unroll 2
+        for (int l = 0; l < std::min(64, lI - 64 * h); ++l) {
+          const int32_t cp = __builtin_amdgcn_readlane(cI[h], l);
+          const double vp = readlane_f64(wI, l);
+          if ((uint32_t)cp >= (uint32_t)kGT) continue;
+          double* row = tile + cp * kGS;
+          const int32_t from = diag ? cp : 0;  // diagonal tile: the upper triangle (c_q >= c_p) only
+          if (cJ[0] >= from) atomicAdd(row + cJ[0], vp * wJ[0]);
+          if (lJ > 64 && cJ[1] >= from) atomicAdd(row + cJ[1], vp * wJ[1]);
+        }
+      }
     }
   }
   __syncthreads();
@@ -216,7 +263,15 @@ __global__ void gram_csr_reduce_kernel(int64_t d, int64_t chunks, const double* 
   const int es = (I == J && a > b) ? b * kGT + a : e;  // below the diagonal: the mirrored entry
   const double* src = partial + (int64_t)blockIdx.y * chunks * (kGT * kGT) + es;
   double acc = 0.0;
-  for (int64_t q = 0; q < chunks; ++q) acc += src[q * (kGT * kGT)];
+  int64_t q = 0;
+  for (; q + 8 <= chunks; q += 8) {  // eight loads in flight, added in order
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = src[(q + u) * (kGT * kGT)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += x[u];
+  }
+  for (; q < chunks; ++q) acc += src[q * (kGT * kGT)];
   B[r * d + c] = acc;
   if (I != J) B[c * d + r] = acc;
 }

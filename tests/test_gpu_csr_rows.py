@@ -50,3 +50,24 @@ def test_csr_row_length_edges(gpu, dtype, kind, n, d):
     rel[o.theta == 0] = np.abs(theta[o.theta == 0])
     print(kind, dtype, n, d, "rank", o.rank, "max rel", rel.max(), flush=True)
     assert rel.max() <= (1e-9 if dtype == torch.float64 else 1e-4)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("kind,n,d", [("edges", 4001, 200), ("edges", 2999, 300), ("short", 4033, 64), ("long", 1030, 512)])
+def test_csr_gram_row_length_edges(gpu, dtype, kind, n, d):
+    """The Gram of sparse rows through the exact scores: rows of one load (at
+    most 64 entries), longer ones, runs past 64 entries in a 128-column block.
+    Bars as for the exact scores of other sparse matrices."""
+    rng = np.random.default_rng(n + d)
+    pool = {"edges": [e for e in EDGES if e <= d] + [d], "short": [0, 1, 2, 3], "long": [64, 65, 130, 300, 512]}[kind]
+    ptr, idx, vals = _matrix(rng.choice(pool, size=n), d, n)
+    A = api.Csr(torch.from_numpy(ptr).to(gpu), torch.from_numpy(idx).to(gpu), torch.from_numpy(vals).to(dtype).to(gpu), n, d)
+    S = sp.csr_matrix((vals, idx, ptr), shape=(n, d))
+    zeta = 1e-10 if dtype == torch.float64 else 1e-5
+    theta = api.lev_estimate(A, 12, 4096, 2 * d, 1, zeta, mode="exact").cpu().numpy().astype(np.float64)
+    o = L.ls_hrn_exact(S, 12, 4096, 2 * d, zeta)
+    live = o.theta > 0
+    assert np.all(theta[~live] == 0)
+    rel = np.abs(theta[live] - o.theta[live]) / o.theta[live]
+    print(kind, dtype, n, d, "rank", o.rank, "exact max rel", rel.max(), flush=True)
+    assert rel.max() < (1e-10 if dtype == torch.float64 else 1e-4)
