@@ -460,11 +460,15 @@ hipError_t launch_grad_f32_kb(const float* a, int64_t n, int64_t d, int64_t ld, 
 //     4 i .. + 3], and column block (q, e) of C^T is the set of columns
 //     64 q + 4 jj + e (jj < 16), un-permuted when C is written out.
 // The KB waves of a stream read the same tile at about the same time, so A
-// comes from HBM once and from L2 otherwise; the second reads are issued
-// after step 1, when the pieces are dead (fewer registers, more waves).  At
-// the end the streams add their C into LDS in stream order and the
-// workgroup writes one partial (the layout and reduction of
-// bwd_gram_kernel).
+// comes from HBM once and from L2 otherwise.  At the end the streams add
+// their C into LDS in stream order and the workgroup writes one partial (the
+// layout and reduction of bwd_gram_kernel).
+// Loads run ahead in the registers that the step before has freed: the
+// second reading of 64 columns goes where their four pieces were as soon as
+// step 1 is past them, and the next tile's pieces where the second reading
+// was as soon as step 3 is past it, so both round trips hide behind MFMAs.
+// Bound by the FP32 MFMAs (330 us of issue at 2^20 x 256, k = 48) and the
+// lockstep of the streams: 598 us, 729 when each reading was waited for.
 constexpr int kYtStride = 80;  // floats per row of the per-wave Y block (16 mod 64 words)
 
 // Tile streams per workgroup: waves spread evenly over the four SIMDs within
@@ -488,7 +492,7 @@ __global__ __launch_bounds__((64 * KB * gram_streams<KB, NJ>()), (KB * gram_stre
     zs[r * kZsStride + c] = Zg[(int64_t)r * kZCols + c];
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = wave % KB, stream = wave / KB;
   const int g = lane >> 4, i16 = lane & 15;
   const int nj = di / 16;
@@ -505,39 +509,52 @@ __global__ __launch_bounds__((64 * KB * gram_streams<KB, NJ>()), (KB * gram_stre
   // fetched from HBM once and found in L2 by the others (drifting apart,
   // each wave fetched its own copy: 2.8x the bytes of A).  The trip count
   // is the workgroup's, the same for every wave.
-  for (int64_t t0 = blockIdx.x; t0 < ntiles; t0 += (int64_t)gridDim.x * S) {
-    const int64_t tile = t0 + (int64_t)stream * gridDim.x;
-    if (tile < ntiles) {
-    // the tile's pieces, row i16 in the lanes: 16 j + 4 g .. + 3
-    const int64_t row = tile * 16 + i16;
+  const int64_t step = (int64_t)gridDim.x * S;
+  const float* zc = zs + 4 * g * kZsStride + 16 * nb + i16;
+  // the pieces 16 j + 4 g .. + 3 of the tile's row i16, j = 4 q .. 4 q + 3
+  float4 a[NJ];
+  auto load_rows = [&](int64_t tile, int q) {
+    const int64_t row = std::min<int64_t>(tile, ntiles - 1) * 16 + i16;
     const float* rp = A + (row < n ? row : 0) * ld + 4 * g;
-    float4 a[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) a[j] = *reinterpret_cast<const float4*>(rp + 16 * (j < nj ? j : 0));
-    const float ws = row < n ? (w != nullptr ? w[row] : 1.0f) : 0.0f;  // w = null: all ones
-    v4f yt = v4f{0.f, 0.f, 0.f, 0.f};
-    const float* zc = zs + 4 * g * kZsStride + 16 * nb + i16;
+    for (int j = 4 * q; j < 4 * q + 4; ++j) a[j] = *reinterpret_cast<const float4*>(rp + 16 * (j < nj ? j : 0));
+  };
+  auto row_weight = [&](int64_t tile) {  // w = null: all ones
+    const int64_t row = std::min<int64_t>(tile, ntiles - 1) * 16 + i16;
+    return row < n ? (w != nullptr ? w[row] : 1.0f) : 0.0f;
+  };
+  const int64_t first = blockIdx.x + (int64_t)stream * gridDim.x;
+  float ws = 0.f;
+  if (ntiles > 0) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      if (j < nj) {
-        const float av[4] = {a[j].x, a[j].y, a[j].z, a[j].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          yt = __builtin_amdgcn_mfma_f32_16x16x4f32(zc[(16 * j + e) * kZsStride], av[e], yt, 0, 0, 0);
-      }
-    }
-    // the tile again, rows in the lane group (columns 64 q + 4 i16 .. + 3;
-    // pieces past d read column 0 and are dropped)
+    for (int q = 0; q < NQ; ++q) load_rows(first, q);
+    ws = row_weight(first);
+  }
+  for (int64_t t0 = blockIdx.x; t0 < ntiles; t0 += step) {
+    const int64_t tile = t0 + (int64_t)stream * gridDim.x;
     float4 rl[4][NQ];
+    v4f yt = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      const int64_t r = tile * 16 + 4 * s4 + g;
-      const float* rq = A + (r < n ? r : 0) * ld;
+    for (int q = 0; q < NQ; ++q) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int c = 64 * q + 4 * i16;
-        rl[s4][q] = *reinterpret_cast<const float4*>(rq + (c < di ? c : 0));
+      for (int j = 4 * q; j < 4 * q + 4; ++j) {
+        if (j < nj) {
+          const float av[4] = {a[j].x, a[j].y, a[j].z, a[j].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            yt = __builtin_amdgcn_mfma_f32_16x16x4f32(zc[(16 * j + e) * kZsStride], av[e], yt, 0, 0, 0);
+        }
       }
+      // the tile again, rows in the lane group (columns 64 q + 4 i16 .. + 3;
+      // pieces past d read column 0 and are dropped), in the place of the
+      // four pieces just used
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) {
+        const int64_t r = std::min<int64_t>(tile, ntiles - 1) * 16 + 4 * s4 + g;
+        const int c = 64 * q + 4 * i16;
+        rl[s4][q] = *reinterpret_cast<const float4*>(A + (r < n ? r : 0) * ld + (c < di ? c : 0));
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
     // Yw[row i16][16 nb + 4 g + v] -> LDS, back as Yw[row 4 s + g][16 nb + i16]
     // (the wave's own block: LDS serves a wave's accesses in order)
@@ -546,9 +563,10 @@ __global__ __launch_bounds__((64 * KB * gram_streams<KB, NJ>()), (KB * gram_stre
     float yop[4];
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) yop[s4] = yb[(4 * s4 + g) * kYtStride + i16];
+    ws = row_weight(tile + step);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      if (q * 4 < nj) {
+      if (q * 4 < nj && tile < ntiles) {
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) {
           const float rv[4] = {rl[s4][q].x, rl[s4][q].y, rl[s4][q].z, rl[s4][q].w};
@@ -557,7 +575,8 @@ __global__ __launch_bounds__((64 * KB * gram_streams<KB, NJ>()), (KB * gram_stre
             cacc[q][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(yop[s4], rv[e], cacc[q][e], 0, 0, 0);
         }
       }
-    }
+      load_rows(tile + step, q);  // the next tile, in the place of the pieces just used
+      __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_barrier();
   }
