@@ -42,8 +42,8 @@ __device__ __forceinline__ double to_f64(__hip_bfloat16 x) { return (double)__bf
 // contiguous in k.  Consecutive threads walk the contiguous index: a thread
 // stages one k of kPerThread rows (KF), or kPerThread k of one row.
 // Every load is unconditional: rows past the operand's end repeat its last
-// row (their products are never stored), and k past the end repeats the last
-// k and is zeroed on the way to LDS, in the last step alone.  (The 64 x 64
+// row (their products are never stored), and k past the end repeats the step's
+// first and is zeroed on the way to LDS, in the last step alone.  (The 64 x 64
 // products over a 256-row sketch: 6.5 us, and 7.8 with a 256-row result; 7.9
 // and 8.8 with a condition and two 64-bit index products on each load.)
 template <bool KF, typename TI>
@@ -51,31 +51,31 @@ struct Stage {
   static constexpr int kRowStep = kThreads / BK, kKStep = kThreads / BM;
   TI v[kPerThread];
   const TI* p;
-  int64_t row[KF ? kPerThread : 1];  // the rows' offsets
+  int64_t off[kPerThread];  // the elements' offsets in a step
   int64_t sk;
   int kk;  // the thread's (first) k
 
   __device__ __forceinline__ void init(int tid, int64_t i0, int64_t rows, const TI* base, int64_t si, int64_t sk_) {
     p = base;
     sk = sk_;
-    if constexpr (KF) {
-      kk = tid % BK;
+    kk = KF ? tid % BK : tid / BM;
 #pragma unroll
-      for (int q = 0; q < kPerThread; ++q) row[q] = std::min<int64_t>(i0 + tid / BK + kRowStep * q, rows - 1) * si;
-    } else {
-      kk = tid / BM;
-      row[0] = std::min<int64_t>(i0 + tid % BM, rows - 1) * si;
+    for (int q = 0; q < kPerThread; ++q) {
+      const int64_t i = i0 + (KF ? tid / BK + kRowStep * q : tid % BM);
+      off[q] = std::min<int64_t>(i, rows - 1) * si + (KF ? kk : kk + kKStep * q) * sk;
     }
   }
   __device__ __forceinline__ void load(int64_t k0, int64_t ke) {
-    if constexpr (KF) {
-      const TI* pk = p + std::min<int64_t>(k0 + kk, ke - 1) * sk;
+    if (k0 + BK > ke) {  // uniform: the last step, where k past the end takes the step's first
 #pragma unroll
-      for (int q = 0; q < kPerThread; ++q) v[q] = pk[row[q]];
-    } else {
-#pragma unroll
-      for (int q = 0; q < kPerThread; ++q) v[q] = (p + std::min<int64_t>(k0 + kk + kKStep * q, ke - 1) * sk)[row[0]];
+      for (int q = 0; q < kPerThread; ++q) {
+        const int k = KF ? kk : kk + kKStep * q;
+        off[q] = k0 + k < ke ? off[q] : off[q] - k * sk;
+      }
     }
+    const TI* pk = p + k0 * sk;  // uniform
+#pragma unroll
+    for (int q = 0; q < kPerThread; ++q) v[q] = pk[off[q]];
   }
   __device__ __forceinline__ void store(int tid, int64_t k0, int64_t ke, double* __restrict__ S) const;
 };
@@ -122,8 +122,11 @@ __device__ __forceinline__ void Stage<KF, TI>::store(int tid, int64_t k0, int64_
 // the XCD of a tile is its row index mod 8, and the triangle loads the low
 // XCDs up to twice as much as the high ones); with one split each upper tile
 // is also stored transposed.
+// (Two waves per SIMD as the bound keep the accumulators in vector registers:
+// with the whole register file on offer the compiler moved them to the
+// accumulation registers and back in every K step.)
 template <bool AK, bool BJ, typename TI = double, bool UPPER = false>
-__global__ __launch_bounds__(kThreads) void dgemm_kernel(int64_t M, int64_t N, int64_t K, double alpha,
+__global__ __launch_bounds__(kThreads, 2) void dgemm_kernel(int64_t M, int64_t N, int64_t K, double alpha,
                                                          const TI* __restrict__ A, int64_t sai,
                                                          int64_t sak, const TI* __restrict__ B,
                                                          int64_t sbk, int64_t sbj, double beta,
