@@ -157,7 +157,7 @@ __device__ void stage_z(const T* __restrict__ Zg, int64_t d, const TileGeom& g, 
 // kb blocks of C are split over grid.y slices; within a slice block j goes to
 // wave j % 4 and stays in its registers for the whole pass.
 template <typename T, bool ZLDS>
-__global__ __launch_bounds__(kThreads) void bwd_gram_kernel(const T* __restrict__ A, int64_t n, int64_t d, int64_t ld,
+__global__ __launch_bounds__(kThreads, 2) void bwd_gram_kernel(const T* __restrict__ A, int64_t n, int64_t d, int64_t ld,
                                                             const T* __restrict__ w, const T* __restrict__ Zg,
                                                             TileGeom g, int blocks_per_slice,
                                                             T* __restrict__ partials) {
@@ -236,7 +236,7 @@ __global__ void bwd_reduce_kernel(const T* __restrict__ partials, int groups, in
 
 // Abar rows of the tile: 2 w_i Y_i Z_full^T + s_i H_full[h(i), :].
 template <typename T, bool ZLDS>
-__global__ __launch_bounds__(kThreads) void bwd_grad_kernel(const T* __restrict__ A, int64_t n, int64_t d, int64_t ld,
+__global__ __launch_bounds__(kThreads, 2) void bwd_grad_kernel(const T* __restrict__ A, int64_t n, int64_t d, int64_t ld,
                                                             const T* __restrict__ w, const T* __restrict__ Zg,
                                                             const T* __restrict__ Hf, HashParams hp, TileGeom g,
                                                             T* __restrict__ G, int64_t ldg) {
@@ -476,8 +476,11 @@ constexpr int kYtStride = 80;  // floats per row of the per-wave Y block (16 mod
 template <int KB, int NJ>
 constexpr int gram_streams() { return NJ <= 4 ? 16 / KB : (KB == 3 ? 4 : (KB == 1 ? 4 : 2)); }
 
+// (At least two waves a SIMD as the bound, also where one runs: with all the
+// registers on offer the compiler moves C to the accumulation registers and
+// back at each tile.)
 template <int KB, int NJ>
-__global__ __launch_bounds__((64 * KB * gram_streams<KB, NJ>()), (KB * gram_streams<KB, NJ>() / 4)) void bwd_gram_f32_kernel(
+__global__ __launch_bounds__((64 * KB * gram_streams<KB, NJ>()), std::max(2, KB * gram_streams<KB, NJ>() / 4)) void bwd_gram_f32_kernel(
     const float* __restrict__ A, int64_t n, int64_t d, int64_t ld, const float* __restrict__ w,
     const float* __restrict__ Zg, float* __restrict__ partials) {
   constexpr int S = gram_streams<KB, NJ>();

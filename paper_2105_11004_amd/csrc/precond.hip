@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kAtvThreads) void lsqr_atv_kernel(const T* __restri
                                                                const double* __restrict__ gpart, int ggroups,
                                                                double* __restrict__ st, int init,
                                                                double* __restrict__ u, double* __restrict__ partial) {
-  constexpr int kW = kAtvThreads / 64, kCols = 64 * V, kAtvIn = V == 1 ? 16 : 8;
+  constexpr int kW = kAtvThreads / 64, kCols = 64 * V, kAtvIn = V == 1 ? 16 : V == 2 ? 8 : 4;
   constexpr int kBatch = kW * kAtvIn;  // rows of a batch over the waves
   __shared__ double red[kW][kCols];
   __shared__ __align__(16) double gs[1024];
