@@ -86,59 +86,117 @@ __host__ size_t lds_bytes(const TileGeom& g, bool zlds) {
 
 // Cooperative load of rows [r0, r0 + TM) of A into As (zero past n and d).
 // Row starts are 16-byte aligned (the interface requires it), so whole
-// 16-byte vectors are read; the vector holding column d-1 is masked.
+// 16-byte vectors are read; the vector holding column d-1 is masked.  Eight
+// vectors a thread are in flight: the loads are unconditional, past the end
+// they take the last row's or the row's first vector.
 template <typename T>
-__device__ void load_tile(const T* __restrict__ A, int64_t n, int64_t d, int64_t ld, int64_t r0,
-                          const TileGeom& g, T* As) {
-  constexpr int E = 16 / sizeof(T);
+__device__ __forceinline__ void load_tile(const T* __restrict__ A, int64_t n, int64_t d, int64_t ld, int64_t r0,
+                                          const TileGeom& g, T* As) {
+  constexpr int E = 16 / sizeof(T), U = 8;
   const int vec_per_row = g.d16 / E;
-  const int total = g.TM * vec_per_row;
-  for (int q = threadIdx.x; q < total; q += kThreads) {
-    const int row = q / vec_per_row;
-    const int c0 = (q % vec_per_row) * E;
-    const int64_t i = r0 + row;
-    T v[E];
-    if (i < n && c0 < d) {
-      const uint4 raw = *reinterpret_cast<const uint4*>(A + i * ld + c0);
-      __builtin_memcpy(v, &raw, 16);
+  const int total = g.TM * vec_per_row;  // at most 2^14
+  // q / vec_per_row by a reciprocal: (q + 1/2) / vec_per_row is at least
+  // 2^-10 from a whole number of at most 64, far beyond its error
+  const float rv = 1.0f / (float)vec_per_row;
+  for (int q0 = threadIdx.x; q0 < total; q0 += U * kThreads) {
+    uint4 raw[U];
+    int at[U], left[U];  // place in As (-1: none), elements before d
 #pragma unroll
-      for (int e = 0; e < E; ++e)
-        if (c0 + e >= d) v[e] = 0;
-    } else {
-#pragma unroll
-      for (int e = 0; e < E; ++e) v[e] = 0;
+    for (int u = 0; u < U; ++u) {
+      const int q = q0 + u * kThreads, qc = std::min(q, total - 1);
+      const int row = (int)(((float)qc + 0.5f) * rv);
+      const int c0 = (qc - row * vec_per_row) * E;
+      const int64_t i = r0 + row;
+      raw[u] = *reinterpret_cast<const uint4*>(A + std::min<int64_t>(i, n - 1) * ld + (c0 < d ? c0 : 0));
+      at[u] = q < total ? row * g.sa + c0 : -1;
+      left[u] = i < n ? (int)d - c0 : 0;
     }
 #pragma unroll
-    for (int e = 0; e < E; ++e) As[row * g.sa + c0 + e] = v[e];
+    for (int u = 0; u < U; ++u) {
+      if (at[u] < 0) continue;
+      T v[E];
+      __builtin_memcpy(v, &raw[u], 16);
+#pragma unroll
+      for (int e = 0; e < E; ++e) As[at[u] + e] = e < left[u] ? v[e] : (T)0;
+    }
   }
 }
 
+// The general passes are bound by latency: a workgroup of four waves walks a
+// tile in steps that wait for memory or LDS (one workgroup a CU in the C pass,
+// two in the other).  So every step keeps several operands in flight; with a
+// load, a wait and a use at a time 2^17 x 250 took 1072 + 1068 us in FP64 (C
+// pass, gradient; Z read from memory) and 810 + 819 in FP32, so 534 + 489 and
+// 341 + 389.
+//
+// acc += sum over s < S of the MFMA of a(s) and z(s), in order; U steps'
+// operands load while the U before them are multiplied (past S they load the
+// last step's and are not used).  S is wave-uniform.
+template <typename T, int U, typename FA, typename FZ>
+__device__ __forceinline__ typename Mfma<T>::Acc mfma_steps(typename Mfma<T>::Acc acc, int S, FA a_at, FZ z_at) {
+  T a0[U], z0[U], a1[U], z1[U];
+  auto load = [&](T(&a)[U], T(&z)[U], int s0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = std::min(s0 + u, S - 1);
+      a[u] = a_at(s);
+      z[u] = z_at(s);
+    }
+  };
+  auto use = [&](const T(&a)[U], const T(&z)[U], int s0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s0 + u < S) acc = Mfma<T>::run(a[u], z[u], acc);
+  };
+  load(a0, z0, 0);
+  for (int s0 = 0;; s0 += 2 * U) {
+    if (s0 + U >= S) {
+      use(a0, z0, s0);
+      break;
+    }
+    load(a1, z1, s0 + U);
+    use(a0, z0, s0);
+    if (s0 + 2 * U >= S) {
+      use(a1, z1, s0 + U);
+      break;
+    }
+    load(a0, z0, s0 + 2 * U);
+    use(a1, z1, s0 + U);
+  }
+  return acc;
+}
+
 // Y (TM x 16 kb) = A_tile Z_full, times scale * w_i, into Ys.  Block b of
-// the (TM/16) x kb grid of 16 x 16 blocks goes to wave b % 4.
+// the (TM/16) x kb grid of 16 x 16 blocks goes to wave b % 4.  Columns of A
+// past d are zero in As, so Z's rows past its last repeat that one.
 template <typename T, bool ZLDS>
-__device__ void tile_y(const T* As, const T* Zs, const T* __restrict__ Zg, int64_t n_zrows, const T* __restrict__ w,
-                       int64_t n, int64_t r0, T scale, const TileGeom& g, T* Ys) {
+__device__ __forceinline__ void tile_y(const T* As, const T* Zs, const T* __restrict__ Zg, int64_t n_zrows,
+                                       const T* __restrict__ w, int64_t n, int64_t r0, T scale, const TileGeom& g,
+                                       T* Ys) {
   using M = Mfma<T>;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int nblk = (g.TM / 16) * g.kb;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nblk = (g.TM / 16) * g.kb, zlast = (int)n_zrows - 1;
   for (int b = wave; b < nblk; b += kWaves) {
     const int mb = b / g.kb, nb = b % g.kb;
-    typename M::Acc acc = {0, 0, 0, 0};
     const T* arow = As + (16 * mb + (lane & 15)) * g.sa + (lane >> 4);
-    for (int s = 0; s < g.d16 / 4; ++s) {
-      const T a = arow[4 * s];
-      const int zr = 4 * s + (lane >> 4), zc = 16 * nb + (lane & 15);
-      const T z = ZLDS ? Zs[zr * g.sz + zc] : (zr < n_zrows ? Zg[(int64_t)zr * kZCols + zc] : (T)0);
-      acc = M::run(a, z, acc);
-    }
+    const int zc = 16 * nb + (lane & 15);
+    T wi[4];  // w = null: all ones
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int row = 16 * mb + M::row(lane, v);
-      const int64_t i = r0 + row;
-      const T wi = i < n ? (w != nullptr ? w[i] : (T)1) : (T)0;  // w = null: all ones
-      Ys[row * g.sy + 16 * nb + (lane & 15)] = acc[v] * wi * scale;
+      const int64_t i = r0 + 16 * mb + M::row(lane, v);
+      wi[v] = w != nullptr ? w[std::min<int64_t>(i, n - 1)] : (T)1;
+      wi[v] = i < n ? wi[v] : (T)0;
     }
+    const typename M::Acc acc = mfma_steps<T, 8>(
+        typename M::Acc{0, 0, 0, 0}, g.d16 / 4, [&](int s) { return arow[4 * s]; },
+        [&](int s) {
+          const int zr = 4 * s + (lane >> 4);
+          return ZLDS ? Zs[zr * g.sz + zc] : Zg[std::min(zr, zlast) * kZCols + zc];
+        });
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      Ys[(16 * mb + M::row(lane, v)) * g.sy + 16 * nb + (lane & 15)] = acc[v] * wi[v] * scale;
   }
 }
 
@@ -169,7 +227,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_gram_kernel(const T* __restri
   stage_z<T, ZLDS>(Zg, d, g, Zs);
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int total_blocks = (g.d16 / 16) * g.kb;
   const int first = blockIdx.y * blocks_per_slice;
   const int last = std::min(total_blocks, first + blocks_per_slice);
@@ -185,14 +243,27 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_gram_kernel(const T* __restri
     __syncthreads();
     tile_y<T, ZLDS>(As, Zs, Zg, d, w, n, r0, (T)1, g, Ys);
     __syncthreads();
+    // (opaque, so that the blocks' addresses are not kept over the whole pass,
+    // where they took the registers of C)
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
 #pragma unroll
     for (int j = 0; j < kMaxCBlocks; ++j) {
       const int b = first + wave + kWaves * j;
       if (b < last) {
         const int db = b / g.kb, nb = b % g.kb;
-        const T* ap = As + (lane >> 4) * g.sa + 16 * db + (lane & 15);
-        const T* yp = Ys + (lane >> 4) * g.sy + 16 * nb + (lane & 15);
-        for (int s = 0; s < g.TM / 4; ++s) acc[j] = M::run(ap[4 * s * g.sa], yp[4 * s * g.sy], acc[j]);
+        const T* ap = As + (ln >> 4) * g.sa + 16 * db + (ln & 15);
+        const T* yp = Ys + (ln >> 4) * g.sy + 16 * nb + (ln & 15);
+        for (int s0 = 0; s0 < g.TM / 4; s0 += 4) {  // (TM is a multiple of 16)
+          T av[4], yv[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            av[u] = ap[4 * (s0 + u) * g.sa];
+            yv[u] = yp[4 * (s0 + u) * g.sy];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[j] = M::run(av[u], yv[u], acc[j]);
+        }
       }
     }
   }
@@ -250,7 +321,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_grad_kernel(const T* __restri
   stage_z<T, ZLDS>(Zg, d, g, Zs);
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t ntiles = (n + g.TM - 1) / g.TM;
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int64_t r0 = t * g.TM;
@@ -273,23 +344,27 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_grad_kernel(const T* __restri
     const int nblk = (g.TM / 16) * (g.d16 / 16);
     for (int b = wave; b < nblk; b += kWaves) {
       const int mb = b % (g.TM / 16), db = b / (g.TM / 16);
-      typename M::Acc acc = {0, 0, 0, 0};
       const T* yp = Ys + (16 * mb + (lane & 15)) * g.sy + (lane >> 4);
-      const int zrow = 16 * db + (lane & 15);
-      for (int s = 0; s < 4 * g.kb; ++s) {
-        const int zc = 4 * s + (lane >> 4);
-        const T z = ZLDS ? Zs[zrow * g.sz + zc] : (zrow < d ? Zg[(int64_t)zrow * kZCols + zc] : (T)0);
-        acc = M::run(yp[4 * s], z, acc);
-      }
-      const int col = 16 * db + (lane & 15);
+      const int zrow = 16 * db + (lane & 15), col = zrow;
+      const int zr = std::min(zrow, (int)d - 1);  // columns past d are not stored
+      // the rows of H_full that this block adds load first
+      T hv[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = 16 * mb + M::row(lane, v);
-        const int64_t i = r0 + row;
-        if (i < n && col < d) {
-          const T hv = Hf[(int64_t)hrow[row] * d + col];
-          G[i * ldg + col] = acc[v] + (srow[row] < 0 ? -hv : hv);
-        }
+        hv[v] = Hf[(int64_t)hrow[row] * d + zr];
+        hv[v] = srow[row] < 0 ? -hv[v] : hv[v];
+      }
+      const typename M::Acc acc = mfma_steps<T, 8>(
+          typename M::Acc{0, 0, 0, 0}, 4 * g.kb, [&](int s) { return yp[4 * s]; },
+          [&](int s) {
+            const int zc = 4 * s + (lane >> 4);
+            return ZLDS ? Zs[zrow * g.sz + zc] : Zg[zr * kZCols + zc];
+          });
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t i = r0 + 16 * mb + M::row(lane, v);
+        if (i < n && col < d) G[i * ldg + col] = acc[v] + hv[v];
       }
     }
   }
