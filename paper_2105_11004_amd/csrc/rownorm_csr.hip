@@ -31,7 +31,7 @@ namespace {
 constexpr int kCsrWaves = 16;
 constexpr int kCsrThreads = 64 * kCsrWaves;
 constexpr int kZStride = 64;  // Z_full row stride in elements (k <= 64)
-constexpr int kRowsPerTask = 64;
+constexpr int kRowsPerTask = 64, kMinRowsPerTask = 8, kTasksPerWave = 2;
 
 template <typename T>
 __device__ __forceinline__ float to_f32(T x);
@@ -116,7 +116,8 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_kernel(const T* __res
                                                                   const int32_t* __restrict__ col_idx,
                                                                   int64_t n, int64_t d, int64_t nnz,
                                                                   const ZT* __restrict__ Zg,
-                                                                  ZT* __restrict__ theta, ColTile ct) {
+                                                                  ZT* __restrict__ theta, ColTile ct,
+                                                                  int rows_per_task) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (col_tile_dead(ct)) return;
   StageEntry<ZT>* stage = reinterpret_cast<StageEntry<ZT>*>(smem);  // [kCsrWaves][64]
@@ -132,11 +133,11 @@ __global__ __launch_bounds__(kCsrThreads) void rownorm_csr_kernel(const T* __res
   }
   StageEntry<ZT>* my = stage + wave * 64;
 
-  const int64_t ntask = (n + kRowsPerTask - 1) / kRowsPerTask;
+  const int64_t ntask = (n + rows_per_task - 1) / rows_per_task;
   for (int64_t task = (int64_t)blockIdx.x * kCsrWaves + wave; task < ntask;
        task += (int64_t)gridDim.x * kCsrWaves) {
-    const int64_t r0 = task * kRowsPerTask;
-    const int64_t r1 = min(n, r0 + kRowsPerTask);
+    const int64_t r0 = task * rows_per_task;  // at most 64 rows
+    const int64_t r1 = min(n, r0 + rows_per_task);
     // lane j holds row_ptr[r0 + j] (j <= r1 - r0; lane 64 would be r1 = r0 + 64)
     // Offsets are clamped to [0, nnz] and row ends to [pos, N1], so a
     // malformed row_ptr yields wrong rows but no stray access or endless loop.
@@ -588,8 +589,6 @@ hipError_t launch_typed(const void* vals, const int64_t* row_ptr, const int32_t*
   const size_t stage_bytes = sizeof(StageEntry<ZT>) * 64 * kCsrWaves;
   const size_t z_bytes = (size_t)d * kZStride * sizeof(ZT);
   constexpr size_t kMaxLds = 144 * 1024;  // leave room below the 160 KB of a CU
-  const int64_t ntask = (n + kRowsPerTask - 1) / kRowsPerTask;
-  const int64_t want = (ntask + kCsrWaves - 1) / kCsrWaves;
   const T* v = static_cast<const T*>(vals);
   const ZT* Z = static_cast<const ZT*>(Zpack);
   ZT* th = static_cast<ZT*>(theta);
@@ -600,24 +599,33 @@ hipError_t launch_typed(const void* vals, const int64_t* row_ptr, const int32_t*
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)gz);
       if (e != hipSuccess) return e;
+      const int64_t want = ((n + 63) / 64 + kCsrWaves - 1) / kCsrWaves;
       const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)num_cu));
       kern<<<grid, kCsrThreads, gz, s>>>(v, row_ptr, col_idx, n, d, nnz, Z, th, ct);
       return hipGetLastError();
     }
   }
-  if (stage_bytes + z_bytes <= kMaxLds) {
-    const size_t lds = stage_bytes + z_bytes;
+  const bool zlds = stage_bytes + z_bytes <= kMaxLds;
+  const size_t lds = zlds ? stage_bytes + z_bytes : stage_bytes;
+  // one workgroup per CU holds the LDS copy of Z_full; a second fits when it is small
+  const int64_t groups = (int64_t)num_cu * (2 * lds <= kMaxLds ? 2 : 1);
+  // A wave works through a task's rows one after the other, so a task's own
+  // length bounds the pass until every wave has two: tasks of 64 rows are
+  // halved down to 8 till then (16 nonzeros a row, 64 rows and this rule:
+  // 325770 x 50 FP64 108 and 72 us, 222824 x 323 FP64 151 and 132, 400001 x
+  // 700 FP32 177 and 156; 1900001 x 200 keeps 64 rows, 615)
+  int rows = kRowsPerTask;
+  while (rows > kMinRowsPerTask && (n + rows - 1) / rows < kTasksPerWave * groups * kCsrWaves) rows /= 2;
+  const int64_t want = ((n + rows - 1) / rows + kCsrWaves - 1) / kCsrWaves;
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, groups));
+  if (zlds) {
     auto kern = rownorm_csr_kernel<T, ZT, true>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    // one workgroup per CU holds the LDS copy of Z_full; a second fits when it is small
-    const int per_cu = (2 * lds <= kMaxLds) ? 2 : 1;
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)num_cu * per_cu));
-    kern<<<grid, kCsrThreads, lds, s>>>(v, row_ptr, col_idx, n, d, nnz, Z, th, ct);
+    kern<<<grid, kCsrThreads, lds, s>>>(v, row_ptr, col_idx, n, d, nnz, Z, th, ct, rows);
   } else {
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)num_cu * 2));
-    rownorm_csr_kernel<T, ZT, false><<<grid, kCsrThreads, stage_bytes, s>>>(v, row_ptr, col_idx, n, d, nnz, Z, th, ct);
+    rownorm_csr_kernel<T, ZT, false><<<grid, kCsrThreads, lds, s>>>(v, row_ptr, col_idx, n, d, nnz, Z, th, ct, rows);
   }
   return hipGetLastError();
 }
