@@ -149,7 +149,8 @@ enum { LEV_SKETCH_GAUSS = 0, LEV_SKETCH_SRHT = 1 };
  * LEV_MODE_QLESS: Algorithm 6: exact scores from a Q-less column-pivoted QR
  *   of A itself (no sketch: m, r_cs and sketch are not used): step j
  *   takes the column of largest remaining norm, forms row j of R from the
- *   column inner products A^T a_p (one pass over A per step) and downdates
+ *   column inner products A^T a_p (a pass over A per step; for dense A with
+ *   d <= 256 per up to sixteen candidate columns at once) and downdates
  *   the norms; it stops before R_jj <= zeta R_00 or after k steps (k is the
  *   step cap here, any k >= 1, at most d steps run).  Then theta_i =
  *   ||e_i^T A P_k R_k^{-1}||^2.  The cutoff is read off downdated norms, so
