@@ -456,13 +456,11 @@ lev_status pivchol_into(double* B, int64_t d, double zeta, const lev::PivCholSta
 // brings it to rounding.
 lev_status cholqr2(int64_t m, int64_t d, const double* X, const double* Rc, const int64_t* r, RefineBufs& b,
                    double* Q, int32_t* err, hipStream_t s) {
-  LEV_HIP(lev::launch_identity(d, b.I, s));
-  LEV_HIP(lev::launch_trsm_z(d, d, Rc, r, b.I, b.Rinv, err, s));  // Rc11^{-1}, zero past r
+  LEV_HIP(lev::launch_trsm_inverse(d, Rc, r, b.I, b.Rinv, err, s));  // Rc11^{-1}, zero past r
   LEV_TRY(gemm_ab(m, d, d, 1.0, X, d, 1, b.Rinv, d, 1, 0.0, b.Qa, b.partial, s));
   LEV_TRY(gemm_ab(d, d, m, 1.0, b.Qa, 1, d, b.Qa, d, 1, 0.0, b.Bq, b.partial, s));
   LEV_TRY(pivchol_into(b.Bq, d, 0.0, b.stf, b.rf, b.permf, b.Rf, s, /*fixed=*/1));
-  LEV_HIP(lev::launch_identity(d, b.I, s));
-  LEV_HIP(lev::launch_trsm_z(d, d, b.Rf, b.rf, b.I, b.Rinv, err, s));
+  LEV_HIP(lev::launch_trsm_inverse(d, b.Rf, b.rf, b.I, b.Rinv, err, s));
   LEV_TRY(gemm_ab(m, d, d, 1.0, b.Qa, d, 1, b.Rinv, d, 1, 0.0, Q, b.partial, s));
   return LEV_OK;
 }
@@ -977,8 +975,7 @@ lev_status lev_estimate_backward(const lev_matrix* A, const lev_params* p, const
   double *I = b.sq[0], *Rinv = b.sq[1], *T1 = b.sq[2], *X = b.sq[3], *Msym = b.sq[4];
   LEV_HIP(lev::launch_gather_zbar(d, k, sv.perm, rank, b.C64, b.Zbar, s));
   LEV_TRY(gemm(d, d, k, b.Zbar, k, 1, sv.Z64, 1, k, T1, b.gemm_partial, s));          // Zbar Z^T
-  LEV_HIP(lev::launch_identity(d, I, s));
-  LEV_HIP(lev::launch_trsm_z(d, d, sv.R, rank, I, Rinv, state_err(sv), s));           // R11^{-1}
+  LEV_HIP(lev::launch_trsm_inverse(d, sv.R, rank, I, Rinv, state_err(sv), s));        // R11^{-1}
   LEV_TRY(gemm(d, d, d, Rinv, 1, d, T1, d, 1, X, b.gemm_partial, s));                 // R11^{-T} T1
   LEV_HIP(lev::launch_neg_triu(d, X, s));                                              // Rbar
   double* M1 = I;

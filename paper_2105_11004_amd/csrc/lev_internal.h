@@ -129,8 +129,12 @@ hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState&
 // over diagonal blocks of 256 and G's rows above the last block are
 // overwritten (they carry the updated right-hand side).
 // err (may be null): bit kErrSolveWait is set if a bounded wait runs out.
+// G null: the identity (d <= 256, k = d).
 hipError_t launch_trsm_z(int64_t d, int64_t k, const double* R, const int64_t* rank, double* G, double* Z64,
                          int32_t* err, hipStream_t s);
+// Z = R11^{-1} (d x d, zero past the rank); work: d x d.
+hipError_t launch_trsm_inverse(int64_t d, const double* R, const int64_t* rank, double* work, double* Z64,
+                               int32_t* err, hipStream_t s);
 
 // Prepares the operand of pass 2: Z_full (d x k, rows indexed by original
 // column, zero off K) converted to the pass-2 compute type and laid out for

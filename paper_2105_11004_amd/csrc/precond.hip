@@ -775,12 +775,10 @@ hipError_t launch_precondition(int method, int64_t d, const double* R, const int
     kernel<<<1, threads, lds, s>>>(d, R, rank, perm, zeta, N, k_out);
     return hipGetLastError();
   }
-  // QR: Z = R11^{-1} (trsm of the identity), rows scattered to the original columns
+  // QR: Z = R11^{-1}, rows scattered to the original columns
   double* I = work;
   double* Z = work + d * d;
-  hipError_t e = launch_identity(d, I, s);
-  if (e != hipSuccess) return e;
-  e = launch_trsm_z(d, d, R, rank, I, Z, err, s);
+  hipError_t e = launch_trsm_inverse(d, R, rank, I, Z, err, s);
   if (e != hipSuccess) return e;
   scatter_rows_kernel<<<(unsigned)((d * d + 255) / 256), 256, 0, s>>>(d, perm, Z, N, rank, k_out);
   return hipGetLastError();

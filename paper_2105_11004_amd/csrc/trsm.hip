@@ -106,7 +106,10 @@ __device__ __forceinline__ void blocked_solve(double* lds, int32_t* ready, int d
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = 16 * w + (lane >> 4) + 4 * v, col = c0 + 16 * cb + (lane & 15);
-        acc[cb][v] = (row < r && col < k) ? G[(unsigned)(row * k + col)] : 0.0;
+        if (G != nullptr)  // uniform; null: the identity
+          acc[cb][v] = (row < r && col < k) ? G[(unsigned)(row * k + col)] : 0.0;
+        else
+          acc[cb][v] = (row < r && row == col) ? 1.0 : 0.0;
       }
   };
   if constexpr (KB <= 3) load_g();
@@ -315,7 +318,8 @@ __device__ __forceinline__ void store_operand(const double* zall, const int32_t*
 // every group has 4 column blocks, the last one possibly partly past k).  G
 // holds the right-hand side of these rows with the contributions of the
 // blocks below already subtracted; the rank is read here, so a block wholly
-// past it writes zero rows of Z.
+// past it writes zero rows of Z.  G null (j0 = 0, d <= 256): the identity,
+// made in registers instead of by a launch of its own.
 __global__ __launch_bounds__(1024) void trsm_blocked_kernel(int64_t d, int64_t k, int64_t j0,
                                                             const double* __restrict__ R,
                                                             const int64_t* __restrict__ rank,
@@ -501,6 +505,17 @@ hipError_t launch_trsm_z(int64_t d, int64_t k, const double* R, const int64_t* r
     }
   }
   return hipGetLastError();
+}
+
+// One launch up to one diagonal block (64 x 64: 5.3 us, where the identity
+// took a launch of 3.2 and the solve 5.3); beyond, the blocks above the last
+// are overwritten with the updated right-hand side, so it is laid out.
+hipError_t launch_trsm_inverse(int64_t d, const double* R, const int64_t* rank, double* work, double* Z64,
+                               int32_t* err, hipStream_t s) {
+  if (d <= kTrsmR) return launch_trsm_z(d, d, R, rank, nullptr, Z64, err, s);
+  hipError_t e = launch_identity(d, work, s);
+  if (e != hipSuccess) return e;
+  return launch_trsm_z(d, d, R, rank, work, Z64, err, s);
 }
 
 namespace {
