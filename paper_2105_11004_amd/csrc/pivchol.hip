@@ -28,11 +28,12 @@
 #include <type_traits>
 
 #include "lev_internal.h"
+#include "panel_slots.h"
 
 namespace lev {
 namespace {
 
-constexpr int NB = 32;
+constexpr int NB = kPanel;
 constexpr int kMaxD = 1024;
 
 typedef double v16d __attribute__((ext_vector_type(16)));
@@ -203,10 +204,12 @@ __device__ __forceinline__ bool static_all(F&& f) {
 //
 // The pivot column's entries of the panel so far are read as two values a lane
 // and broadcast by the FMAs themselves (fma_rows), not as LDS broadcasts per
-// entry.  Every column's last SH entries are kept in LDS, so that each wave
+// entry.  Every column's last SH + 1 entries are kept in LDS, so that each wave
 // reads the pivot's as soon as it knows the pivot, with no second barrier; with
 // SH = 16 (d > kShareD, where 32 do not fit) the column's owner posts those of
-// the first half behind a second barrier in the second half's steps.  The
+// the first half behind a second barrier in the steps past 16.  That no step
+// writes over a slot that it reads is argued, and checked when this is
+// compiled, in panel_slots.h.  The
 // latency of the pivot's row of S (about 800 cycles) is covered by the sums,
 // which are added to it last.  Bound: the chain of one step, about 2000 cycles
 // (wave maximum 440, barrier 90, the waves' maximum 365, the row of S 800, the
@@ -217,8 +220,6 @@ constexpr int kPanelCols = 2;
 constexpr int kPanelThreads = kMaxD / kPanelCols;
 constexpr int kPanelWaves = kPanelThreads / 64;
 constexpr int kShareD = 600;
-// stride of a column's entries in LDS (the writes spread over the banks)
-constexpr int rc_stride(int sh) { return sh + 1; }
 
 // FIXED: the pivot order is the identity (step J's only candidate is column J).
 template <bool FIXED, int SH>
@@ -227,9 +228,9 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
                                                                       PivCholState st,
                                                                       int64_t* __restrict__ rank_out,
                                                                       const double* __restrict__ ref_r00) {
-  static_assert(SH == 16 || SH == NB, "a half or the whole panel");
-  extern __shared__ double rc[];  // d x rc_stride(SH)
-  __shared__ double post[16];     // SH = 16: the pivot's entries of the first half
+  static_assert(SH == kPanelHalf || SH == NB, "a half or the whole panel");
+  extern __shared__ double rc[];  // d x panel_stride(SH)
+  __shared__ double post[kPanelHalf];  // SH = 16: the pivot's entries of the first half
   __shared__ double wv[2][kPanelWaves];
   __shared__ int wi[2][kPanelWaves];
 
@@ -258,6 +259,8 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
   int mine = 0;  // wave 0: lane j keeps pivot j
   const int q0 = c0 < di ? c0 : 0, q1 = c0 + 1 < di ? c0 + 1 : 0;  // in bounds
   const bool pair = c0 + 1 < di && (di & 1) == 0;                  // 16-byte aligned (d even, c0 even)
+  const int slot_lo = lane & 15;                                   // entries 0 .. 15 (= panel_slot) and 16 .. 31
+  const int slot_hi = panel_slot(SH, kPanelHalf + (lane & 15));
   const bool whole = static_all<NB>([&](auto jc) __attribute__((always_inline)) -> bool {
     constexpr int j = decltype(jc)::value;
     if (J >= di) return false;
@@ -316,20 +319,15 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
     // column's entries of the panel so far
     const double s0 = S[p * di + q0], s1 = S[p * di + q1];
     double blo = 0.0, bhi = 0.0;
-    if constexpr (SH == NB) {
-      if (j > 0) blo = rc[p * rc_stride(SH) + (lane & 15)];
-      if (j > 16) bhi = rc[p * rc_stride(SH) + 16 + (lane & 15)];
-    } else {
-      if (j > 0 && j <= 16) blo = rc[p * rc_stride(SH) + (lane & 15)];
-      if (j > 16) {
-        bhi = rc[p * rc_stride(SH) + (lane & 15)];
-        if ((p >> 1) == tid) {
+    if (j > 0 && !panel_posted(SH, j)) blo = rc[p * panel_stride(SH) + slot_lo];
+    if (j > kPanelHalf) bhi = rc[p * panel_stride(SH) + slot_hi];
+    if constexpr (panel_posted(SH, j)) {
+      if ((p >> 1) == tid) {
 #pragma unroll
-          for (int t = 0; t < 16; ++t) post[t] = (p & 1) ? rp1[t] : rp0[t];
-        }
-        lds_barrier();
-        blo = post[lane & 15];
+        for (int t = 0; t < kPanelHalf; ++t) post[t] = (p & 1) ? rp1[t] : rp0[t];
       }
+      lds_barrier();
+      blo = post[lane & 15];
     }
     double inv, rjj;
     rsqrt_sqrt(pv, &inv, &rjj);
@@ -348,8 +346,8 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
     }
     rp0[j] = val[0];
     rp1[j] = val[1];
-    if (c0 < di) rc[c0 * rc_stride(SH) + j % SH] = val[0];
-    if (c0 + 1 < di) rc[(c0 + 1) * rc_stride(SH) + j % SH] = val[1];
+    if (c0 < di) rc[c0 * panel_stride(SH) + panel_slot(SH, j)] = val[0];
+    if (c0 + 1 < di) rc[(c0 + 1) * panel_stride(SH) + panel_slot(SH, j)] = val[1];
     double* rrow = st.Rrows + J * di + c0;
     if (pair) {
       *reinterpret_cast<double2*>(rrow) = make_double2(val[0], val[1]);
@@ -935,8 +933,8 @@ hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState&
   const int threads = (int)(((d + 64 * kPanelCols - 1) / (64 * kPanelCols)) * 64);
   const bool all = d <= kShareD;
   auto panel = all ? (fixed ? pivchol_panel_kernel<true, NB> : pivchol_panel_kernel<false, NB>)
-                   : (fixed ? pivchol_panel_kernel<true, 16> : pivchol_panel_kernel<false, 16>);
-  const size_t lds = sizeof(double) * (size_t)d * (all ? rc_stride(NB) : rc_stride(16));
+                   : (fixed ? pivchol_panel_kernel<true, kPanelHalf> : pivchol_panel_kernel<false, kPanelHalf>);
+  const size_t lds = sizeof(double) * (size_t)d * panel_stride(all ? NB : kPanelHalf);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(panel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
