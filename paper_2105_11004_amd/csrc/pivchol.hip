@@ -61,20 +61,22 @@ __device__ __forceinline__ double wave_max_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 
-// Max over the 64 lanes of a signed word, in every lane of the result
-// (uniform).
+// The same over signed words.  (The builtins, not inline assembly: the compiler
+// sees the cross-lane moves and the scalar that the last of them writes, and
+// places the wait states they need before it is compared with.)
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ int dpp_max_step(int v) {
+  const int s = __builtin_amdgcn_update_dpp(INT32_MIN, v, CTRL, ROWMASK, 0xF, false);
+  return v > s ? v : s;
+}
 __device__ __forceinline__ int wave_max_i32(int v) {
-  int m;
-  asm volatile(
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_readlane_b32 %1, %0, 63"
-      : "+v"(v), "=s"(m));
-  return m;
+  v = dpp_max_step<0x111, 0xF>(v);
+  v = dpp_max_step<0x112, 0xF>(v);
+  v = dpp_max_step<0x114, 0xF>(v);
+  v = dpp_max_step<0x118, 0xF>(v);
+  v = dpp_max_step<0x142, 0xA>(v);
+  v = dpp_max_step<0x143, 0xC>(v);
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // The largest v over the 64 lanes (no NaN) and the lowest lane holding it.
@@ -117,14 +119,10 @@ __device__ __forceinline__ double max8_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ int max8_i32(int v) {
-  int m;
-  asm volatile(
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_readlane_b32 %1, %0, 7"
-      : "+v"(v), "=s"(m));
-  return m;
+  v = dpp_max_step<0x111, 0xF>(v);
+  v = dpp_max_step<0x112, 0xF>(v);
+  v = dpp_max_step<0x114, 0xF>(v);
+  return __builtin_amdgcn_readlane(v, 7);
 }
 
 // 1 / sqrt(x) (hardware estimate and two Newton steps) and sqrt(x) from it
