@@ -239,12 +239,13 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
   if (J0 > 0 && st.flags[0] != 0) return;
   const int di = (int)d, Ji = (int)J0;  // d <= kMaxD: 32-bit offsets below
 
-  double dg[2];  // -inf: not alive (a pivot before, past d, or NaN)
+  double dg[2];
+  bool alive[2];  // not a pivot before, nor past d; a NaN diagonal is alive (its entries of R are NaN) and never wins
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int c = c0 + q;
     dg[q] = (c < di) ? ((J0 == 0) ? S[(int64_t)c * d + c] : st.diag[c]) : -INFINITY;
-    dg[q] = fmax(dg[q], -INFINITY);
+    alive[q] = dg[q] != -INFINITY;
   }
   double r00 = ref_r00 != nullptr ? *ref_r00 : ((J0 == 0) ? 0.0 : *st.r00);
   // the cutoff sqrt(pv) > zeta r00 is tested as pv > (zeta r00)^2, so that
@@ -265,8 +266,8 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
     // the lane's candidate (a column no longer alive holds -inf; fixed
     // order: the only candidate of step J is column J); a NaN diagonal
     // never wins
-    const double m0 = (!FIXED || c0 == J) ? dg[0] : -INFINITY;
-    const double m1 = (!FIXED || c0 + 1 == J) ? dg[1] : -INFINITY;
+    const double m0 = fmax((!FIXED || c0 == J) ? dg[0] : -INFINITY, -INFINITY);
+    const double m1 = fmax((!FIXED || c0 + 1 == J) ? dg[1] : -INFINITY, -INFINITY);
     const bool second = m1 > m0;
     const double mv = second ? m1 : m0;
     // the wave's: high words first (as in wave_argmax); the winning lane posts
@@ -338,9 +339,10 @@ __global__ __launch_bounds__(kPanelThreads) void pivchol_panel_kernel(const doub
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const bool piv = c0 + q == p;
-      const double nd = fmax(fma(-val[q], val[q], dg[q]), -INFINITY);  // (-inf stays, a NaN leaves)
-      val[q] = piv ? rjj : (dg[q] != -INFINITY ? val[q] : 0.0);
-      dg[q] = piv ? -INFINITY : nd;
+      const double nd = fma(-val[q], val[q], dg[q]);
+      val[q] = piv ? rjj : (alive[q] ? val[q] : 0.0);
+      dg[q] = piv ? -INFINITY : (alive[q] ? nd : dg[q]);
+      alive[q] = alive[q] && !piv;
     }
     rp0[j] = val[0];
     rp1[j] = val[1];
