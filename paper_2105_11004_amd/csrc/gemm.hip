@@ -358,7 +358,7 @@ hipError_t launch_gram_dense(int dtype, const void* A, int64_t n, int64_t d, int
                              double* partial, double* B, hipStream_t s) {
   if (d <= 0) return hipSuccess;
   if (splits < 1) splits = 1;
-  const int parts = gram_tall_partials(n, d, ld, dtype == 0 ? 8 : dtype == 1 ? 4 : 2, splits);
+  const int parts = gram_tall_partials(A, n, d, ld, dtype == 0 ? 8 : dtype == 1 ? 4 : 2, splits);
   if (parts > 0) return launch_gram_tall(dtype, A, n, d, ld, parts, partial, B, s);
   int64_t kchunk = (n + splits - 1) / splits;
   kchunk = std::max<int64_t>(BK, ((kchunk + BK - 1) / BK) * BK);

@@ -208,8 +208,12 @@ void launch(const TI* A, int64_t n, int d, int64_t ld, int parts, double* partia
 // square), so it needs a third of the CUs to win: 96 workgroups, which n of
 // about 50 000 gives (exact scores at 65536 x 63 FP32, 127 workgroups: 184 us
 // against 428; 100003 x 200 FP64: 1.05 ms against 1.21).
-int gram_tall_partials(int64_t n, int64_t d, int64_t ld, int64_t elt, int splits) {
-  if (d > 256 || splits < 2 || (ld * elt) % 16 != 0) return 0;
+// A's rows are read as 16-byte pieces, so its base and pitch have to be whole
+// ones: the interface asks that of A, but not of a sketch handed to
+// lev_rank_estimate, which may start 8 bytes off (the tiled form reads
+// elements).
+int gram_tall_partials(const void* A, int64_t n, int64_t d, int64_t ld, int64_t elt, int splits) {
+  if (d > 256 || splits < 2 || (ld * elt) % 16 != 0 || reinterpret_cast<uintptr_t>(A) % 16 != 0) return 0;
   const int64_t room = (int64_t)splits * 2 * d / (d + 1);
   const int64_t parts = std::min<int64_t>(256, room);
   return parts >= 96 && n >= 64 * parts ? (int)parts : 0;

@@ -234,7 +234,7 @@ hipError_t launch_gram_dense(int dtype, const void* A, int64_t n, int64_t d, int
 int gram_dense_splits(int64_t n, int64_t d);
 // The tall form of launch_gram_dense (gram_tall.hip): partial triangles that
 // fit the same room, or 0 where the tiled form is to run.
-int gram_tall_partials(int64_t n, int64_t d, int64_t ld, int64_t elt, int splits);
+int gram_tall_partials(const void* A, int64_t n, int64_t d, int64_t ld, int64_t elt, int splits);
 hipError_t launch_gram_tall(int dtype, const void* A, int64_t n, int64_t d, int64_t ld, int parts, double* partial,
                             double* B, hipStream_t s);
 // Splits (>= 2) for the sketch's Gram through launch_gram_dense (FP64 A~, m rows).

@@ -1,0 +1,45 @@
+"""The Gram of a tall matrix reads 16-byte pieces, so it is taken only for a base
+and a row pitch of whole ones: the rule on the CPU, and lev_rank_estimate on a
+sketch that starts 8 bytes off, long enough for that form.  Bar: 1e-9 R_00 as
+in the other tests of the factor."""
+
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import leverage as L
+from paper_2105_11004_amd import api
+
+
+def test_tall_gram_only_for_aligned_rows():
+    rule = getattr(api.load_library(), "_ZN3lev18gram_tall_partialsEPKvlllli")
+    rule.argtypes = [ctypes.c_void_p, *[ctypes.c_int64] * 4, ctypes.c_int]
+    base = 1 << 20
+    assert rule(base, 9000, 64, 64, 8, 64) >= 96
+    assert rule(base + 16, 9000, 64, 64, 8, 64) >= 96
+    for off in (2, 4, 8, 12):
+        assert rule(base + off, 9000, 64, 64, 8, 64) == 0
+    assert rule(base, 9000, 63, 63, 8, 64) == 0  # the second row starts 8 bytes off
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("offset", [0, 1])
+def test_rank_estimate_of_a_sketch_off_alignment(gpu, offset):
+    print("sketch off alignment", offset, flush=True)
+    m, d, rank = 9000, 64, 40
+    rng = np.random.default_rng(5)
+    At = rng.standard_normal((m, rank)) @ rng.standard_normal((rank, d))
+    room = torch.empty(m * d + 2, dtype=torch.float64, device=gpu)
+    view = room[offset:offset + m * d].view(m, d)
+    view.copy_(torch.from_numpy(At))
+    assert view.data_ptr() % 16 == 8 * offset
+    perm, R, r = api.lev_rank_estimate(view, 1e-5)
+    o = L.qrcp_sign_normalised(At, 1e-5)
+    assert int(r.item()) == o.rank == rank
+    perm, R = perm.cpu().numpy(), R.cpu().numpy()
+    np.testing.assert_array_equal(perm[:rank], o.perm[:rank])
+    want = np.empty((rank, d))
+    want[:, o.perm] = o.R[:rank]
+    np.testing.assert_allclose(R[:rank], want[:, perm], atol=1e-9 * o.R[0, 0], rtol=0)
