@@ -217,7 +217,14 @@ __device__ __forceinline__ bool static_all(F&& f) {
 constexpr int kPanelCols = 2;
 constexpr int kPanelThreads = kMaxD / kPanelCols;
 constexpr int kPanelWaves = kPanelThreads / 64;
-constexpr int kShareD = 600;
+// The whole panel of every column in LDS as far as it goes (no second barrier: a
+// panel takes 29.8 us at 619 columns, where that ends, 32.5 at 620; the whole
+// factorisation 730 and 779).
+constexpr int kLdsBytes = 160 * 1024;  // of a CU: one workgroup
+constexpr int kPanelStaticLds =        // post, wv and wi below
+    kPanelHalf * (int)sizeof(double) + 2 * kPanelWaves * (int)(sizeof(double) + sizeof(int));
+constexpr int kShareD = (kLdsBytes - kPanelStaticLds) / (panel_stride(NB) * (int)sizeof(double));  // 619
+static_assert((int)sizeof(double) * kMaxD * panel_stride(kPanelHalf) + kPanelStaticLds <= kLdsBytes, "any d fits");
 
 // FIXED: the pivot order is the identity (step J's only candidate is column J).
 template <bool FIXED, int SH>
