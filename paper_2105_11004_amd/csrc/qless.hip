@@ -685,12 +685,18 @@ int qless_groups(int64_t n, bool csr) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(cap, (n + per - 1) / per));
 }
 
+// The block form's workgroups, and the rows of d partial sums that its passes
+// (or the squares before them) write.
+static int block_groups(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kBlkGroups, (n + 63) / 64)); }
+static size_t block_partial_rows(int64_t n) {
+  return (size_t)std::max(qless_groups(n, false), block_groups(n) * kBlk);
+}
+
 size_t qless_ws_doubles(int64_t n, int64_t d, int64_t kmax, bool csr) {
   if (!csr && d <= kBlkD)
     // s, Rrow, partial (of the squares or of a block), rows, sums, dctl (2)
     // and, as doubles, sel, have, piv, block and ctl
-    return (size_t)d + (size_t)kmax * d +
-           (size_t)std::max(qless_groups(n, false), kBlkGroups * kBlk) * d + (size_t)d * d + (size_t)kBlk * d + 2 +
+    return (size_t)d + (size_t)kmax * d + block_partial_rows(n) * d + (size_t)d * d + (size_t)kBlk * d + 2 +
            2 * (size_t)d + (size_t)kmax + kBlk + 4;
   // s, Rrow, partial, dctl (2) and, as doubles, sel, piv and ctl
   return (size_t)d + (size_t)kmax * d + (size_t)qless_groups(n, csr) * d + 2 + (size_t)d + (size_t)kmax + 4;
@@ -709,7 +715,7 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
   int32_t* piv = sel + d;
   int64_t* ctl = reinterpret_cast<int64_t*>(reinterpret_cast<double*>(sel) + d + kmax);
   if (!csr && d <= kBlkD)  // behind the block form's dctl (below)
-    ctl = reinterpret_cast<int64_t*>(partial + (size_t)std::max(groups, kBlkGroups * kBlk) * d + d * d + kBlk * d + 2);
+    ctl = reinterpret_cast<int64_t*>(partial + block_partial_rows(n) * d + d * d + kBlk * d + 2);
   hipError_t e = launch_fill_zero(ctl, 4 * sizeof(int64_t), st);
   if (e != hipSuccess) return e;
   if (n == 0) {  // no pass writes them
@@ -740,7 +746,7 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
     BlockState bs;
     bs.s = s;
     bs.Rrow = Rrow;
-    bs.rows = partial + (size_t)std::max(groups, kBlkGroups * kBlk) * d;
+    bs.rows = partial + block_partial_rows(n) * d;
     bs.sums = bs.rows + d * d;
     bs.dctl = bs.sums + kBlk * d;
     bs.ctl = ctl;
@@ -749,7 +755,7 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
     bs.piv = bs.have + d;
     bs.block = bs.piv + kmax;
     qless_block_step_kernel<<<(unsigned)((d + 63) / 64), 256, 0, st>>>((int)d, kmax, groups, (int)d, partial, zeta, 1, bs);
-    const int bg = (int)std::max<int64_t>(1, std::min<int64_t>(kBlkGroups, (n + 63) / 64));
+    const int bg = block_groups(n);
     // every pass takes at least one step, so kmax of them always suffice; those
     // after the stop return at once
     for (int64_t j = 0; j < kmax; ++j) {
