@@ -518,7 +518,10 @@ __global__ __launch_bounds__(kAtvThreads) void lsqr_atv_kernel(const T* __restri
 // z).  The square roots and divisions are long FP64 sequences, so the last
 // wave alone takes the rotation and the columns' own waves alpha; run by all
 // sixteen waves they filled the SIMDs.
-// d = 60, 196 partials: 6.0 us (15.7 with one thread a column).
+// d = 60, 196 partials: 6.0 us (15.7 with one thread a column).  Beyond 256
+// columns N is read twice, 2 d^2 doubles by one workgroup, and what counts is
+// how many of its loads are in flight: d = 400, 600 and 1000: 70, 140 and 275 us
+// (97, 220 and 590 with a load's address and wait in every turn of the loops).
 template <int C>
 __global__ __launch_bounds__(C == 64 ? 512 : 1024) void lsqr_step_kernel(
     int64_t d, const double* __restrict__ N, const double* __restrict__ partial, int groups, double* __restrict__ st,
@@ -534,7 +537,8 @@ __global__ __launch_bounds__(C == 64 ? 512 : 1024) void lsqr_step_kernel(
   __shared__ double red[C / 64];
   __shared__ double sc[4];  // phi / rho, sin, cos, rho
   const int di = (int)d;
-  const int c = threadIdx.x & (C - 1), p = threadIdx.x / C;
+  const int c = threadIdx.x & (C - 1);
+  const int p = __builtin_amdgcn_readfirstlane(threadIdx.x / C);  // (C is whole waves: rows of N and partials are uniform)
   const int cl = c < di ? c : 0;  // columns past d load column 0 and are dropped
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -612,11 +616,22 @@ __global__ __launch_bounds__(C == 64 ? 512 : 1024) void lsqr_step_kernel(
 #pragma unroll
       for (int q = 0; q < 7; ++q) sp[0] = 8 * dw + q < di ? fma(nr[q], g[std::min(8 * dw + q, C - 1)], sp[0]) : sp[0];
   } else {
-#pragma unroll 4
-    for (int k = 0; k < dw; ++k)
+    // kQ rows of each chain in flight (past the last they load it again)
+    constexpr int kQ = 16 / kU;
+    const int end = __builtin_amdgcn_readfirstlane(c) < di ? dw : 0;  // (a wave wholly past d has none)
+    for (int k0 = 0; k0 < end; k0 += kQ) {
+      double a[kQ][kU];
 #pragma unroll
-      for (int u = 0; u < kU; ++u)
-        sp[u] = fma(N[(int64_t)(8 * k + p * kU + u) * d + cl], g[8 * k + p * kU + u], sp[u]);
+      for (int q = 0; q < kQ; ++q)
+#pragma unroll
+        for (int u = 0; u < kU; ++u) a[q][u] = N[(int64_t)(8 * std::min(k0 + q, dw - 1) + p * kU + u) * d + cl];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q)
+        if (k0 + q < dw) {  // uniform
+#pragma unroll
+          for (int u = 0; u < kU; ++u) sp[u] = fma(a[q][u], g[8 * (k0 + q) + p * kU + u], sp[u]);
+        }
+    }
     if (p == 0)
       for (int i = 8 * dw; i < di; ++i) sp[0] = fma(N[(int64_t)i * d + cl], g[i], sp[0]);
   }
@@ -676,11 +691,33 @@ __global__ __launch_bounds__(C == 64 ? 512 : 1024) void lsqr_step_kernel(
       if (gl == 0 && r < di) z[r] = zr;
     }
   } else {
-    for (int r = wave; r < di; r += kWaves) {
+    // a row's loads and the next row's in flight together; a lane past d takes
+    // column 0 and adds nothing (a branch around the pieces past d cost more
+    // than their loads)
+    constexpr int kC = C / 64;
+    double a[2][kC];
+    auto load = [&](auto set, int r) {
+      const double* row = N + (int64_t)std::min(r, di - 1) * d;
+#pragma unroll
+      for (int j = 0; j < kC; ++j) a[decltype(set)::value][j] = row[lane + 64 * j < di ? lane + 64 * j : 0];
+    };
+    auto use = [&](auto set, int r) {
       double zr = 0.0;
-      for (int cc = lane; cc < di; cc += 64) zr = fma(N[(int64_t)r * d + cc], g[cc], zr);
+#pragma unroll
+      for (int j = 0; j < kC; ++j)
+        zr = lane + 64 * j < di ? fma(a[decltype(set)::value][j], g[lane + 64 * j], zr) : zr;
       zr = wave_sum(zr);
       if (lane == 0) z[r] = zr;
+    };
+    const std::integral_constant<int, 0> s0;
+    const std::integral_constant<int, 1> s1;
+    load(s0, wave);
+    for (int r = wave; r < di; r += 2 * kWaves) {
+      load(s1, r + kWaves);
+      use(s0, r);
+      if (r + kWaves >= di) break;
+      load(s0, r + 2 * kWaves);
+      use(s1, r + kWaves);
     }
   }
   if (own) {
