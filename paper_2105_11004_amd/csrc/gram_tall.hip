@@ -204,10 +204,16 @@ void launch(const TI* A, int64_t n, int d, int64_t ld, int parts, double* partia
 // Partial triangles (workgroups) of the tall form within the room of
 // `splits` full d x d partials, or 0 where the tiled form is the better one.
 // The tall form keeps one workgroup a CU busy, at three to four times the
-// tiled form's rate, and gets about 2 splits of them (a triangle is half a
+// tiled form's rate on FP32 and BF16, and gets about 2 splits of them (a triangle is half a
 // square), so it needs a third of the CUs to win: 96 workgroups, which n of
 // about 50 000 gives (exact scores at 65536 x 63 FP32, 127 workgroups: 184 us
 // against 428; 100003 x 200 FP64: 1.05 ms against 1.21).
+// FP64 A is not widened, so there the tiled form does better once the triangle
+// is large against its fixed cost, a wider reduction: with fewer than 160
+// workgroups it is taken beyond 192 columns, and beyond 128 for more than 2^16
+// rows (rank of a 101- to 127-workgroup sketch, tall and tiled: 24000 x 200 303
+// and 279 us, 400000 x 256 1546 and 947; 40000 x 160 232 and 246, 400000 x 160 787
+// and 715).
 // A's rows are read as 16-byte pieces, so its base and pitch have to be whole
 // ones: the interface asks that of A, but not of a sketch handed to
 // lev_rank_estimate, which may start 8 bytes off (the tiled form reads
@@ -216,7 +222,10 @@ int gram_tall_partials(const void* A, int64_t n, int64_t d, int64_t ld, int64_t 
   if (d > 256 || splits < 2 || (ld * elt) % 16 != 0 || reinterpret_cast<uintptr_t>(A) % 16 != 0) return 0;
   const int64_t room = (int64_t)splits * 2 * d / (d + 1);
   const int64_t parts = std::min<int64_t>(256, room);
-  return parts >= 96 && n >= 64 * parts ? (int)parts : 0;
+  if (parts < 96 || n < 64 * parts) return 0;
+  // FP64 with fewer than 160 workgroups: see above
+  if (elt == 8 && parts < 160 && (d > 192 || (d > 128 && n > 65536))) return 0;
+  return (int)parts;
 }
 
 hipError_t launch_gram_tall(int dtype, const void* A, int64_t n, int64_t d, int64_t ld, int parts, double* partial,

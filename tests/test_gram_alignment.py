@@ -24,6 +24,17 @@ def test_tall_gram_only_for_aligned_rows():
     assert rule(base, 9000, 63, 63, 8, 64) == 0  # the second row starts 8 bytes off
 
 
+@pytest.mark.parametrize("n,d,elt,splits,tall", [
+    (24000, 200, 8, 51, False), (400000, 256, 8, 51, False), (40000, 160, 8, 64, True), (400000, 160, 8, 64, False),
+    (65536, 192, 8, 64, True), (65537, 192, 8, 64, False), (1 << 20, 128, 8, 64, True), (100000, 256, 8, 128, True),
+    (50000, 256, 4, 64, True), (50000, 256, 2, 64, True), (8000, 64, 8, 64, False), (9000, 64, 8, 47, False)])
+def test_tall_gram_where_it_is_the_faster_form(n, d, elt, splits, tall):
+    """The sizes at which both forms were timed, and the rule's own edges."""
+    rule = getattr(api.load_library(), "_ZN3lev18gram_tall_partialsEPKvlllli")
+    rule.argtypes = [ctypes.c_void_p, *[ctypes.c_int64] * 4, ctypes.c_int]
+    assert (rule(1 << 20, n, d, d, elt, splits) > 0) == tall
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("offset", [0, 1])
 def test_rank_estimate_of_a_sketch_off_alignment(gpu, offset):
