@@ -203,6 +203,7 @@ struct QlessInput {
   int64_t n, d, ld, nnz;
 };
 int qless_groups(int64_t n, bool csr);
+bool qless_in_blocks(int64_t n, int64_t d, int64_t kmax, int64_t elt);  // dense A: the form the steps take
 size_t qless_ws_doubles(int64_t n, int64_t d, int64_t kmax, bool csr);
 hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, double* ws, int32_t* perm_out,
                            double* R_out, int64_t* rank_out, hipStream_t st);

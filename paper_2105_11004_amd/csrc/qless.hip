@@ -13,7 +13,8 @@
 // Dense A with d <= 256 columns: the rows b are formed for a block of 16
 // columns a pass, those of largest remaining norm (qless_block_pass_kernel);
 // the steps then go on as long as the next pivot's row is there.  Every result
-// is the same quantity; only the number of passes falls.
+// is the same quantity; only the number of passes falls.  (A few steps over a
+// few columns: qless_in_blocks.)
 //
 // Else, per step: one pass kernel over A writes per-workgroup partial sums of b
 // (dense: 16-byte row vectors with the pivot element as weight; CSR: the
@@ -685,6 +686,24 @@ int qless_groups(int64_t n, bool csr) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(cap, (n + per - 1) / per));
 }
 
+// Whether the columns are taken in blocks.  A block pass stages 64 columns at
+// least, whatever d is, and does not tell on how few steps they are spent; a
+// pass of the plain form costs its bytes, little where they come from a cache.
+// So a cap of a few steps over a few columns takes the plain form, from the row
+// count on at which it was the faster one (below that the launches are what
+// counts).  Plain and in blocks, us a call: FP32, 4 steps, 2^20 x 16 157 and 212,
+// 2^20 x 32 213 and 224, 2^20 x 64 399 and 288; 8 steps of 8 columns 131000 rows
+// 120 and 111, 524000 151 and 165; one column, 2^20 rows 89 and 188; FP64, 4 steps of
+// 32 columns, 131000 rows 97 and 105, 2^20 354 and 315; 2 steps of 64, 33000 rows
+// 75 and 88.
+bool qless_in_blocks(int64_t n, int64_t d, int64_t kmax, int64_t elt) {
+  if (d > kBlkD) return false;
+  if (n < (d < 8 ? 65536 : 10000)) return true;
+  if (d <= 8 && n >= 400000) return false;
+  if (d > 64 || kmax * (d + 32) > 256) return true;
+  return kmax > 2 && kmax * d * elt > 512 && n * d * elt > 32 << 20;
+}
+
 // The block form's workgroups, and the rows of d partial sums that its passes
 // (or the squares before them) write.
 static int block_groups(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kBlkGroups, (n + 63) / 64)); }
@@ -693,7 +712,7 @@ static size_t block_partial_rows(int64_t n) {
 }
 
 size_t qless_ws_doubles(int64_t n, int64_t d, int64_t kmax, bool csr) {
-  if (!csr && d <= kBlkD)
+  if (!csr && d <= kBlkD)  // (the block form's room, whichever form runs)
     // s, Rrow, partial (of the squares or of a block), rows, sums, dctl (2)
     // and, as doubles, sel, have, piv, block and ctl
     return (size_t)d + (size_t)kmax * d + block_partial_rows(n) * d + (size_t)d * d + (size_t)kBlk * d + 2 +
@@ -714,7 +733,8 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
   int32_t* sel = reinterpret_cast<int32_t*>(dctl + 2);
   int32_t* piv = sel + d;
   int64_t* ctl = reinterpret_cast<int64_t*>(reinterpret_cast<double*>(sel) + d + kmax);
-  if (!csr && d <= kBlkD)  // behind the block form's dctl (below)
+  const bool blocks = !csr && qless_in_blocks(n, d, kmax, in.dtype == 0 ? 8 : in.dtype == 1 ? 4 : 2);
+  if (blocks)  // behind the block form's dctl (below)
     ctl = reinterpret_cast<int64_t*>(partial + block_partial_rows(n) * d + d * d + kBlk * d + 2);
   hipError_t e = launch_fill_zero(ctl, 4 * sizeof(int64_t), st);
   if (e != hipSuccess) return e;
@@ -742,7 +762,7 @@ hipError_t launch_qless_qr(const QlessInput& in, int64_t kmax, double zeta, doub
     }
   };
   if ((e = pass(1)) != hipSuccess) return e;
-  if (!csr && d <= kBlkD) {
+  if (blocks) {
     BlockState bs;
     bs.s = s;
     bs.Rrow = Rrow;
