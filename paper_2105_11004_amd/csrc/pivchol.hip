@@ -692,9 +692,10 @@ __global__ __launch_bounds__(768) void pivchol_small_kernel(const double* __rest
 // short loop body per block.  Each entry is one chain over the pivots in
 // order from the lower triangle's value, and R_JJ is the pivot times its
 // reciprocal root, as in the workgroup form, so both give the same bits.  The
-// other waves load the Gram and write the pivoted R.  Bound: the chain of one pivot step in one wave (maximum, LDS
-// read, FMAs, reciprocal root; about 0.45 us).  At d = 64, 48 pivots: 26 us in
-// one launch, against 44 + 5 us for the workgroup form below and the
+// other waves load the Gram and write the pivoted R.  Bound: the chain of one
+// pivot step in one wave (maximum, LDS read, FMAs, reciprocal root; about 0.45
+// us).  At d = 64, 48 pivots: 26 us in
+// one launch, against 44 + 5 us for the workgroup form above and the
 // permutation's own launch; past 64 columns a lane would hold two.
 constexpr int kWaveD = 64;
 constexpr int kWaveS = kWaveD + 2;  // row stride of the Gram in LDS
@@ -916,14 +917,14 @@ __global__ __launch_bounds__(256) void schur_update_kernel(double* __restrict__ 
       }
 }
 
-}  // namespace
-
-static hipError_t launch_pivchol_finalize(int64_t d, const PivCholState& st, const int64_t* rank,
-                                   int32_t* perm_out, double* R_out, hipStream_t s) {
+hipError_t launch_pivchol_finalize(int64_t d, const PivCholState& st, const int64_t* rank, int32_t* perm_out,
+                                   double* R_out, hipStream_t s) {
   pivchol_finalize_kernel<<<(unsigned)((d + kFinalRows - 1) / kFinalRows), kMaxD, 0, s>>>(d, st, rank, perm_out,
                                                                                           R_out);
   return hipGetLastError();
 }
+
+}  // namespace
 
 hipError_t launch_pivchol(double* B, int64_t d, double zeta, const PivCholState& st, int64_t* rank_out,
                           int32_t* perm_out, double* R_out, hipStream_t s, int fixed, const double* ref_r00) {

@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kStepThreads) void qless_step_kernel(int64_t d, int
 // multiply-adds, 0.13 ms at 2^20 x 256 against 0.18 ms for the read).  The next
 // pivots are mostly among the columns of largest remaining norm, so a block
 // serves several steps: at 2^20 x 256 FP32, rank 16, three block passes of
-// 225 us in place of 16 passes of 244 us (4.98 -> 1.5 ms a call).  Two
+// 225 us in place of 16 passes of 244 us.  Two
 // workgroups a CU with 32 rows of A in flight each (one with 64 rows: 265 us).
 constexpr int kBlk = 16;
 constexpr int kBlkD = 256;
@@ -704,12 +704,12 @@ bool qless_in_blocks(int64_t n, int64_t d, int64_t kmax, int64_t elt) {
   return kmax > 2 && kmax * d * elt > 512 && n * d * elt > 32 << 20;
 }
 
+namespace {
 // The block form's workgroups, and the rows of d partial sums that its passes
 // (or the squares before them) write.
-static int block_groups(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kBlkGroups, (n + 63) / 64)); }
-static size_t block_partial_rows(int64_t n) {
-  return (size_t)std::max(qless_groups(n, false), block_groups(n) * kBlk);
-}
+int block_groups(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(kBlkGroups, (n + 63) / 64)); }
+size_t block_partial_rows(int64_t n) { return (size_t)std::max(qless_groups(n, false), block_groups(n) * kBlk); }
+}  // namespace
 
 size_t qless_ws_doubles(int64_t n, int64_t d, int64_t kmax, bool csr) {
   if (!csr && d <= kBlkD)  // (the block form's room, whichever form runs)

@@ -333,9 +333,10 @@ hipError_t launch_dense_typed(const void* A, int64_t n, int64_t d, int64_t ld, c
 // are summed in a fixed order at the end.
 //
 // Bound by the gather: a bucket's rows lie anywhere in A, so each costs whole
-// 64-byte lines of row_ptr, col_idx and vals (2.1 GB for the 1.2 GB of 2^23 x
-// 512 at 16 nonzeros a row), beside a row's ~20 vector instructions (half of
-// the issue slots).  No load may wait for another: with a conversion or a
+// 128-byte lines of row_ptr, col_idx and vals (35 million reads of 128 bytes at
+// L2, 4.5 GB, for the 1.2 GB of 2^23 x 512 at 16 nonzeros a row; more than HBM
+// delivers in the time, so the 256 MB cache behind L2 holds a part), beside a
+// row's ~20 vector instructions (half of the issue slots).  No load may wait for another: with a conversion or a
 // select next to it under `if (lane < length)` the compiler waited for every
 // load in turn and the pass took 1332 us; all loads unconditional, 747;
 // and the next U rows in flight while these are added, 675.  More waves (64
