@@ -207,13 +207,13 @@ __device__ __forceinline__ bool static_all(F&& f) {
 // SH = 16 (d > kShareD, where 32 do not fit) the column's owner posts those of
 // the first half behind a second barrier in the steps past 16.  That no step
 // writes over a slot that it reads is argued, and checked when this is
-// compiled, in panel_slots.h.  The
-// latency of the pivot's row of S (about 800 cycles) is covered by the sums,
-// which are added to it last.  Bound: the chain of one step, about 2000 cycles
-// (wave maximum 440, barrier 90, the waves' maximum 365, the row of S 800, the
-// entry and diagonal 300).  A panel of 32: 26.5 us at d = 512, 30.7 at 520, 40.0
-// at 1024 (33.2, 38.3 and 44.7 with LDS broadcasts, two barriers a step, a
-// scaled square root and division, and maxima over doubles).
+// compiled, in panel_slots.h.  The latency of the pivot's row of S (about 800
+// cycles) is covered by the sums, which are added to it last.  Bound: the chain of
+// one step, about 2000 cycles at d = 512 (wave maximum 440, barrier 90, the waves'
+// maximum 365, the row of S 800, the entry and diagonal 300).  A panel of 32: 27.5
+// us at d = 512, 30 at 520, 32 to 37 at 1024 (33.2, 38.3 and 44.7 with LDS
+// broadcasts, two barriers a step, a scaled square root and division, and maxima
+// over doubles).
 constexpr int kPanelCols = 2;
 constexpr int kPanelThreads = kMaxD / kPanelCols;
 constexpr int kPanelWaves = kPanelThreads / 64;
